@@ -307,9 +307,12 @@ enum { FQ_DENSE_VALU = 128 };
 fq_status fq_workspace_bytes(const fq_problem* pr, size_t* bytes);
 
 /*
- * fq_launch_config -- the launch the fused entry point would make for pr and
- * a Tile-COO with the given buckets_per_tile (1..256) and group_mode (for
- * tools and benchmarks; nothing is launched).  Outputs (host):
+ * fq_launch_config -- the strip kernel's launch for pr and a Tile-COO with the
+ * given buckets_per_tile (1..256) and group_mode (for tools and benchmarks;
+ * nothing is launched).  It is the launch the fused entry point makes with at
+ * most 16 rows, with a forced split or a schedule or strip switch, and where
+ * workgroups would get few tiles; with more rows and a long K, the row-block
+ * kernel runs instead, whose grid these fields do not describe.  Outputs (host):
  *   cfg[0] strip width in columns (32 or 64)   cfg[1] K ranges per strip (split)
  *   cfg[2] dense waves per workgroup           cfg[3] outlier-only waves per workgroup
  *   cfg[4] outlier mapping (FQ_SPARSE_GATHER or FQ_SPARSE_MFMA)

@@ -508,7 +508,7 @@ def fq_debug_decode_tile_coo(tc: TileCOODevice, K: int, N: int, stream=None):
 def fq_launch_config(M: int, K: int, N: int, split_k: int = 0, sparse: str = "auto",
                      flags: int = 0, buckets_per_tile: int | None = None,
                      group_mode: int | None = None) -> dict:
-    """The launch the fused entry point would make (nothing is launched) for a
+    """The strip kernel's launch (nothing is launched; see fq.h for when it runs) for a
     Tile-COO packed with the given bucket count and grouping (default: the
     library's default packing)."""
     lib = load()

@@ -28,7 +28,7 @@ GEMM_SOURCES = ["gemm_ref.cpp"]
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 
 HOST_SOURCES = ["capi.cpp", "tilecoo.cpp", "quant.cpp"]
-HIP_SOURCES = ["kernels.hip"]
+HIP_SOURCES = ["kernels.hip", "rows.hip"]
 
 # Packed-fp32 VALU forms are kept out of every HIP object.  MFMA results stay
 # in ordinary VGPRs (the accumulation registers would need a copy-out per

@@ -27,6 +27,12 @@ constexpr int kMaxStrips = int(kCounterRegion / 4);
 // 4 MiB of them).
 constexpr size_t kScratchBytes = kCounterRegion + (size_t(8) << 20);
 
+// The row-block kernel (rows.hip) serves more rows than this, with at least so
+// many tiles per workgroup and partial sums that the static scratch holds.
+constexpr int kRowsMinM = 16;
+constexpr int kRowsMinTiles = 14;
+constexpr size_t kRowsPartialLimit = kScratchBytes - kCounterRegion;
+
 // Launch plan of one matmul kernel.  Everything that sizes the workspace
 // depends only on (M, K, N, split_k) so the workspace can be sized before the
 // Tile-COO exists.
@@ -54,6 +60,10 @@ struct Plan {
   size_t slot_bytes, off_shc, off_flag, off_trash, off_xs, lds_bytes;
   // workspace layout, bytes: counters at 0, partial sums at kCounterRegion
   size_t partial_bytes, ws_bytes;
+  // the row-block kernel's launch (rows.hip), where it is the one to run:
+  // 32-row blocks per workgroup (0: the strip kernel runs), row blocks of M,
+  // K ranges and workgroups per row block
+  int rows_RB, rows_blocks, rows_S, rows_G;
 };
 
 // Schedule options of make_plan (bit set).
@@ -83,6 +93,11 @@ struct MatmulPtrs {
   int y_f32;
   void* workspace;
 };
+
+// Adds the row-block kernel's launch to a plan made without a forced split or
+// schedule switch, where that kernel is the faster one (rows.hip).
+void plan_rows(Plan* plan);
+int launch_rows(const Plan& plan, const MatmulPtrs& p, bool sparse, void* stream);
 
 // Enqueues one matmul kernel; returns a hipError_t value (0 on success).
 int launch_matmul(const Plan& plan, const MatmulPtrs& p, bool dense, bool sparse, void* stream);

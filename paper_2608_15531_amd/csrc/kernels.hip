@@ -213,28 +213,6 @@ struct TileRegs {
   uint32_t g0, g1; // the tile's group range
 };
 
-// Every operand is read with raw buffer loads: a resource descriptor per
-// array (base and byte size, wave-uniform), a per-lane byte offset fixed for
-// the whole kernel, and a wave-uniform byte offset that moves from tile to
-// tile.  Address arithmetic therefore stays in scalar registers; the plan
-// keeps every array below 2^31 bytes.
-constexpr int kBufferWord3 = 0x00020000;   // raw 32-bit elements, no swizzle (gfx9)
-constexpr int kSc1 = 16;                   // cache-policy operand: device (agent) scope
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, int(bytes), kBufferWord3);
-}
-
-__device__ __forceinline__ uint4 buf_load16(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-  return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, int(voff), int(soff), 0));
-}
-__device__ __forceinline__ uint2 buf_load8(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-  return __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(r, int(voff), int(soff), 0));
-}
-__device__ __forceinline__ uint32_t buf_load4(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-  return __builtin_amdgcn_raw_buffer_load_b32(r, int(voff), int(soff), 0);
-}
-
 template <int MB>
 struct Operands {
   __amdgpu_buffer_rsrc_t w, s, z, x, g;
@@ -375,23 +353,6 @@ __device__ __forceinline__ void bulk_tile(BulkRegs<NCB>& b, int tt, int c,
   }
 }
 
-// Calls f(integral_constant<int, I>) for I = B .. E-1, in order.
-template <int B, int E, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (B < E) {
-    f(std::integral_constant<int, B>{});
-    static_for<B + 1, E>(f);
-  }
-}
-
-// s_waitcnt with only the vector-memory counter constrained (gfx9 encoding:
-// vmcnt low bits [3:0], high bits [15:14]; expcnt and lgkmcnt left at max).
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
-}
-
 __device__ __forceinline__ void store_out(const MatmulArgs& a, int m, int n, f32x4_t v) {
   const size_t idx = size_t(m) * a.N + n;
   if (a.y_addend) {
@@ -462,129 +423,6 @@ __device__ __forceinline__ void sparse_gather(const MatmulArgs& a, const uint16_
                   bf16_bits_to_f32(xr[(p4 >> (8 * j)) & 0xFFu]) * bf16_bits_to_f32(v));
     }
   }
-}
-
-// MFMA mode: the B-operand image of a strip's tile (128 rows x 16 NCB
-// columns).  Local column n' of the strip belongs to MFMA column block
-// j = n' % NCB at position c = n' / NCB, so element (k, n') is read by lane
-// (c + 16 * ((k%32)/8)) as B of MFMA (step k/32, block j), at the position its
-// X partner holds k (chunk order x0,x4,x1,x5,...).  As a bf16 index into the
-// wave's image its bits are, for 64-column strips (NCB = 4, 16 KB image)
-//   0: k2 | 1-2: k0,k1 | 3-6: n'2..n'5 | 7-8: k3,k4 | 9-10: n'0,n'1 | 11-12: k5,k6
-// and for 32-column strips (NCB = 2, 8 KB image)
-//   0: k2 | 1-2: k0,k1 | 3-6: n'1..n'4 | 7-8: k3,k4 | 9: n'0 | 10-11: k5,k6.
-// image_offsets forms the four byte offsets of a group at once, one slot per
-// byte lane while the index is split into its low and high bytes, then two
-// slots per dword (16-bit halves; the offsets are below 2^14).  C holds the
-// Tile-COO columns (0..63); a 32-column strip uses their low five bits.
-template <int NCB>
-__device__ __forceinline__ void image_offsets(uint32_t R, uint32_t C, uint32_t& o01, uint32_t& o23) {
-  const uint32_t r1 = R << 1, r2 = R >> 2;
-  uint32_t lo = r2 & 0x01010101u;               // k2
-  lo = and_or(r1, 0x06060606u, lo);             // k0, k1
-  uint32_t hi = (R >> 4) & 0x01010101u;         // k4
-  if constexpr (NCB == 4) {
-    const uint32_t c1 = C << 1;
-    lo = and_or(c1, 0x78787878u, lo);           // n'2..n'5
-    hi = and_or(c1, 0x06060606u, hi);           // n'0, n'1
-    hi = and_or(r2, 0x18181818u, hi);           // k5, k6
-  } else {
-    lo = and_or(C << 2, 0x78787878u, lo);       // n'1..n'4
-    hi = and_or(C << 1, 0x02020202u, hi);       // n'0
-    hi = and_or(R >> 3, 0x0C0C0C0Cu, hi);       // k5, k6
-  }
-  lo = and_or(R << 4, 0x80808080u, lo);         // k3
-  // [lo0 hi0 lo1 hi1] and [lo2 hi2 lo3 hi3], then element -> byte offset
-  o01 = __builtin_amdgcn_perm(hi, lo, 0x05010400u) << 1;
-  o23 = __builtin_amdgcn_perm(hi, lo, 0x07030602u) << 1;
-}
-
-// The same slots as full LDS byte addresses, for images that lie below
-// 64 KB of LDS at a 256-byte-aligned base: the byte-lane assembly builds byte
-// offsets (the bit layouts above shifted up by one) and ORs the base's high
-// byte, replicated in `base_rep`, into the high bytes, where its bits lie
-// above the offset's.  Each 16-bit half is then a whole address.
-template <int NCB>
-__device__ __forceinline__ void image_addresses(uint32_t R, uint32_t C, uint32_t base_rep,
-                                                uint32_t& a01, uint32_t& a23) {
-  const uint32_t r1 = R >> 1, r3 = R >> 3;
-  uint32_t lo = r1 & 0x02020202u;                 // k2
-  lo = and_or(R << 2, 0x0C0C0C0Cu, lo);           // k0, k1
-  uint32_t hi = and_or(r3, 0x03030303u, base_rep);   // k3, k4
-  if constexpr (NCB == 4) {
-    const uint32_t c2 = C << 2;
-    lo = and_or(c2, 0xF0F0F0F0u, lo);             // n'2..n'5
-    hi = and_or(c2, 0x0C0C0C0Cu, hi);             // n'0, n'1
-    hi = and_or(r1, 0x30303030u, hi);             // k5, k6
-  } else {
-    lo = and_or(C << 3, 0xF0F0F0F0u, lo);         // n'1..n'4
-    hi = and_or(C << 2, 0x04040404u, hi);         // n'0
-    hi = and_or(R >> 2, 0x18181818u, hi);         // k5, k6
-  }
-  a01 = __builtin_amdgcn_perm(hi, lo, 0x05010400u);
-  a23 = __builtin_amdgcn_perm(hi, lo, 0x07030602u);
-}
-
-typedef __attribute__((address_space(3))) uint16_t lds_u16;
-
-// 16-bit LDS store at an absolute LDS byte address.
-__device__ __forceinline__ void lds_store16(uint32_t addr, uint32_t v) {
-  *reinterpret_cast<lds_u16*>(uintptr_t(addr)) = uint16_t(v);
-}
-
-// LDS byte address where a dynamic-LDS pointer points.
-__device__ __forceinline__ uint32_t lds_address(const void* p) {
-  return uint32_t(reinterpret_cast<uintptr_t>(
-      (__attribute__((address_space(3))) const unsigned char*)(p)));
-}
-
-// Writes a group's four values into the image at absolute LDS address `img`
-// and returns where they went.  A padding slot (value bits 0) goes to the
-// trash word instead, since its position may coincide with a real element of
-// another group, and so does a slot whose column lies in the other half of a
-// 64-column Tile-COO tile when the strip is 32 columns wide (`half` = which
-// half this strip is; bit 5 of a column selects the half).
-// With FA the addresses come whole from image_addresses (`img` then holds
-// the replicated base byte instead of the base).
-template <int NCB, bool FA>
-__device__ __forceinline__ void group_addresses(uint32_t img, uint32_t R, uint32_t C,
-                                                uint32_t o[4]) {
-  uint32_t o01, o23;
-  if constexpr (FA) {
-    image_addresses<NCB>(R, C, img, o01, o23);
-    o[0] = o01 & 0xFFFFu;
-    o[1] = o01 >> 16;
-    o[2] = o23 & 0xFFFFu;
-    o[3] = o23 >> 16;
-  } else {
-    image_offsets<NCB>(R, C, o01, o23);
-    o[0] = img + (o01 & 0xFFFFu);
-    o[1] = img + (o01 >> 16);
-    o[2] = img + (o23 & 0xFFFFu);
-    o[3] = img + (o23 >> 16);
-  }
-}
-
-template <int NCB, bool FA>
-__device__ __forceinline__ void scatter_group(uint32_t img, uint32_t trash, uint4 raw,
-                                              uint32_t half, uint32_t addr[4]) {
-  uint32_t o[4];
-  group_addresses<NCB, FA>(img, raw.x, raw.y, o);
-  // per slot: bit 5 of its column equals `half` (always true for NCB = 4)
-  const uint32_t other = NCB == 4 ? 0u : ((raw.y >> 5) ^ (half * 0x01010101u)) & 0x01010101u;
-  addr[0] = (raw.z & 0xFFFFu) != 0u && !(other & 0x1u) ? o[0] : trash;
-  addr[1] = raw.z > 0xFFFFu && !(other & 0x100u) ? o[1] : trash;
-  addr[2] = (raw.w & 0xFFFFu) != 0u && !(other & 0x10000u) ? o[2] : trash;
-  addr[3] = raw.w > 0xFFFFu && !(other & 0x1000000u) ? o[3] : trash;
-  lds_store16(addr[0], raw.z);
-  lds_store16(addr[1], raw.z >> 16);
-  lds_store16(addr[2], raw.w);
-  lds_store16(addr[3], raw.w >> 16);
-}
-
-__device__ __forceinline__ void clear_group(const uint32_t addr[4]) {
-#pragma unroll
-  for (int j = 0; j < 4; ++j) lds_store16(addr[j], 0u);
 }
 
 // Two 16-row blocks hold the most registers; they are kept to two waves per
@@ -1668,6 +1506,7 @@ bool make_plan(int M, int K, int N, int split_k, bool dense, bool sparse, int B,
   const size_t lim = size_t(1) << 31;
   if (size_t(K) * N / 2 >= lim || size_t(M) * K * 2 >= lim || p.partial_bytes >= lim) return false;
   p.ws_bytes = kCounterRegion + align_up(p.partial_bytes, 256);
+  if (dense && split_k == 0 && opts == 0 && mode != 0) plan_rows(&p);
   *pl = p;
   return true;
 }
@@ -1702,6 +1541,7 @@ int launch_matmul(const Plan& pl, const MatmulPtrs& p, bool dense, bool sparse, 
     if (dense) sparse = false;
     else a.packed = reinterpret_cast<const uint4*>(p.workspace);
   }
+  if (pl.rows_RB && dense && !p.y_addend) return launch_rows(pl, p, sparse, stream);
   if (pl.MODE == 0) return fqk::launch_mode<1, 0>(pl, a, dense, sparse, s);
   if (pl.MB == 1) return fqk::launch_mode<1, 1>(pl, a, dense, sparse, s);
   return fqk::launch_mode<2, 1>(pl, a, dense, sparse, s);

@@ -1,0 +1,82 @@
+"""The row-block kernel (more than 16 rows, long K) at the edges of its range.
+
+Exact-arithmetic inputs: every fp32 sum is exact in any order, so the result
+equals the fp64 oracle bit for bit on sampled columns (the first and last of
+the 32-, 64- and 128-column blocks among them) and, on every column, the strip
+kernel's, which a forced strip width selects.
+"""
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from synth import make_exact_problem
+
+pytestmark = pytest.mark.gpu
+
+# (M, K, N, outlier share, packing): the kernel runs where every workgroup gets
+# at least 14 tiles; the workgroups are ceil(N / 128) column blocks x 64-row
+# blocks (32-row ones up to 32 rows), split along K to at most 256
+CASES = [
+    (33, 1792, 16448, 0.02, None),        # 14 tiles, no split, N an odd multiple of 64
+    (64, 7296, 8192, 0.01, None),         # 57 tiles split 4 ways: 14 and 15
+    (65, 1920, 8320, 0.03, "column"),     # two row blocks, 15 tiles (the K groups take 8 and 7)
+    (128, 2176, 8256, 0.06, None),        # more than 64 groups in a tile, last block half empty
+    (96, 14336, 512, 0.0004, None),       # split 16 ways, most tiles empty
+    (17, 1792, 16512, 0.02, None),        # one 32-row block
+    (32, 2048, 16448, 0.05, "column"),    # one full 32-row block, more than 64 groups
+    (40, 16256, 4096, 0.0, None),         # no outliers: the dense-only form
+]
+
+
+@pytest.mark.parametrize("M,K,N,frac,packing", CASES, ids=[f"rows{i}" for i in range(len(CASES))])
+def test_rows_kernel_bit_exact(gpu_lib, M, K, N, frac, packing):
+    fq = gpu_lib
+    p = make_exact_problem(M, K, N, frac=frac, seed=M + N)
+    X, Wq, s, z = fq.to_device(p)
+    params = {"buckets_per_tile": 16, "group_mode": fq.FQ_GROUP_BY_COLUMN} if packing else None
+    tc = fq.TileCOODevice(fq.fq_pack_tile_coo(K, N, p.k, p.n, p.v, params))
+    print(f"rows kernel M={M} K={K} N={N} outliers {frac}", flush=True)
+    y = fq.fq_w4a16_outlier_matmul(X, Wq, s, z, tc, y_dtype="f32")
+    again = fq.fq_w4a16_outlier_matmul(X, Wq, s, z, tc, y_dtype="f32")
+    noalloc = torch.empty_like(y)
+    fq.fq_w4a16_outlier_matmul_noalloc(X, Wq, s, z, tc, noalloc, y_dtype="f32")
+    bf = fq.fq_w4a16_outlier_matmul(X, Wq, s, z, tc)
+    strip = fq.fq_w4a16_outlier_matmul(X, Wq, s, z, tc, y_dtype="f32", flags=fq.FQ_STRIP_64)
+    dense = fq.fq_w4a16_matmul(X, Wq, s, z, y_dtype="f32")
+    dense_strip = fq.fq_w4a16_matmul(X, Wq, s, z, y_dtype="f32", flags=fq.FQ_STRIP_64)
+    torch.cuda.synchronize()
+    assert torch.equal(y, again) and torch.equal(y, noalloc)
+    assert torch.equal(y, strip) and torch.equal(dense, dense_strip)
+    assert torch.equal(bf, y.to(torch.bfloat16))
+    cols = np.unique(np.concatenate([[0, 1, 31, 32, 63, 64, 127, 128, N - 65, N - 64, N - 33, N - 32, N - 1],
+                                     np.random.default_rng(M).choice(N, 32, replace=False)]) % N)
+    exact = oracle.matmul(p.X, p.Wq, p.scales, p.zeros, K, N, p.group, p.k, p.n, p.v, cols)
+    assert np.array_equal(y.cpu().numpy()[:, cols], exact.astype(np.float32))
+
+
+def test_rows_kernel_graph_replays(gpu_lib):
+    """Replays of a captured split-K launch leave the counters at zero and
+    repeat the eager result, with eager calls on the same workspace between."""
+    fq = gpu_lib
+    M, K, N = 64, 7296, 8192
+    p = make_exact_problem(M, K, N, frac=0.01, seed=3)
+    X, Wq, s, z = fq.to_device(p)
+    tc = fq.TileCOODevice(fq.fq_pack_tile_coo(K, N, p.k, p.n, p.v))
+    ws = torch.zeros(fq.fq_workspace_bytes(M, K, N), dtype=torch.uint8, device="cuda")
+    eager = fq.fq_w4a16_outlier_matmul(X, Wq, s, z, tc, y_dtype="f32", ws=ws)
+    torch.cuda.synchronize()
+    Y = torch.empty_like(eager)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        fq.fq_w4a16_outlier_matmul(X, Wq, s, z, tc, Y=Y, y_dtype="f32", ws=ws)
+    for _ in range(4):
+        Y.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(Y, eager)
+        assert int(ws[:256 * 1024].count_nonzero()) == 0
+        other = fq.fq_w4a16_outlier_matmul(X, Wq, s, z, tc, y_dtype="f32", ws=ws)
+        torch.cuda.synchronize()
+        assert torch.equal(other, eager)
