@@ -67,7 +67,7 @@ def kernel_name(fq, M, K, N, packing=None, flags=0):
     bk = "true" if c["bulk_scales"] else "false"
     dv = "true" if flags & fq.FQ_DENSE_VALU else "false"
     return (f"matmul_kernel<{mb}, {mode}, {c['strip_cols'] // 16}, true, true, "
-            f"{c['dense_waves']}, {sk}, {c['outlier_waves']}, {xs}, {bk}, {dv}>")
+            f"{c['dense_waves']}, {sk}, {c['outlier_waves']}, {xs}, {bk}, {dv}, 1>")
 
 
 def dominant_kernel(fq, cases):
@@ -697,13 +697,13 @@ def trace_summary(stats_csv, traced_log, plain_log):
            "(by-bucket groups, one bucket per tile; the paper-format step of the same run, "
            "by-column groups with 16 buckets, is included in the counts); 8 rotated weight "
            "copies per shape (graph replay).", "",
-           "`matmul_kernel<MB, MODE, NCB, DENSE, SPARSE, NW, SK, NWS, XR, BK, DV>`: MB 16-row "
+           "`matmul_kernel<MB, MODE, NCB, DENSE, SPARSE, NW, SK, NWS, XR, BK, DV, GL>`: MB 16-row "
            "blocks; MODE 0 = LDS-gather outlier mapping, 1 = MFMA image mapping; NCB 16-column "
            "MFMA blocks per strip (2: 32-column strips, 4: 64-column strips); NW waves per "
            "workgroup; SK Stream-K; NWS extra outlier-only waves; XR row-wise X loads per tile "
            "reordered through LDS (ceil(M/4); 0 = loads in operand order); BK scales and "
            "zero-points loaded once per wave; DV dense products by VALU dot products "
-           "(ablation).", "",
+           "(ablation); GL loads of 64 outlier groups per tile.", "",
            f"Kernel sources sha256 (kernels.hip, device.hpp, internal.hpp): "
            f"`{kernel_source_digest()}`", "",
            "| kernel | launches (shapes, default packing) | calls | total ns | average ns | min ns "

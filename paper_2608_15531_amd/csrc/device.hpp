@@ -344,10 +344,12 @@ __device__ __forceinline__ void slot_masks(uint4 raw, uint32_t half, uint32_t& m
 
 template <int NCB, bool FA>
 __device__ __forceinline__ void scatter_group(uint32_t img, uint32_t trash, uint4 raw,
-                                              uint32_t half, uint32_t addr[4]) {
+                                              uint32_t half, uint32_t use, uint32_t addr[4]) {
   uint32_t o[4], m01, m23;
   group_addresses<NCB, FA>(img, raw.x, raw.y, o);
   slot_masks<NCB>(raw, half, m01, m23);
+  m01 &= use;   // all ones, or zero: every slot to the trash word
+  m23 &= use;
   addr[0] = bit_select(uint32_t(int32_t(m01 << 16) >> 16), o[0], trash);
   addr[1] = bit_select(uint32_t(int32_t(m01) >> 16), o[1], trash);
   addr[2] = bit_select(uint32_t(int32_t(m23 << 16) >> 16), o[2], trash);

@@ -31,6 +31,7 @@ constexpr size_t kScratchBytes = kCounterRegion + (size_t(8) << 20);
 // many tiles per workgroup and partial sums that the static scratch holds.
 constexpr int kRowsMinM = 16;
 constexpr int kRowsMinTiles = 14;
+constexpr int kRowsMaxGroups = 160;   // of the largest tile
 constexpr size_t kRowsPartialLimit = kScratchBytes - kCounterRegion;
 
 // Launch plan of one matmul kernel.  Everything that sizes the workspace
@@ -54,6 +55,7 @@ struct Plan {
   int B;             // buckets per tile
   int XS;            // row-wise X loads per tile through the LDS stage: 0, or 1, 2, 4 (ceil(M/4))
   int BK;            // 1: a dense wave loads the scales and zero-points of all its tiles at once
+  int64_t max_tile_groups;   // the caller's largest group count of a tile
   int DV;            // 1: dense products by VALU dot products instead of MFMA (one row; ablation)
   // dynamic LDS layout, bytes: one slot per wave (X slice or B-operand
   // image), then the gather-mode sparse output buffers or the X stages
@@ -97,7 +99,8 @@ struct MatmulPtrs {
 // Adds the row-block kernel's launch to a plan made without a forced split or
 // schedule switch, where that kernel is the faster one (rows.hip).
 void plan_rows(Plan* plan);
-int launch_rows(const Plan& plan, const MatmulPtrs& p, bool sparse, void* stream);
+int launch_rows(const Plan& plan, const MatmulPtrs& p, bool sparse, bool two_group_loads,
+                void* stream);
 
 // Enqueues one matmul kernel; returns a hipError_t value (0 on success).
 int launch_matmul(const Plan& plan, const MatmulPtrs& p, bool dense, bool sparse, void* stream);

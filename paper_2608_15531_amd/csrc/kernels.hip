@@ -160,6 +160,7 @@ struct MatmulArgs {
   const uint32_t* tile_indptr;
   const uint4* packed;
   int64_t n_groups;
+  int two_group_loads; // host only: pick the instance with GL = 2
   int y_f32;
   int slot_bytes;      // one wave's LDS slot
   int off_shc;         // per-wave sparse output buffers (gather mode)
@@ -172,20 +173,20 @@ struct MatmulArgs {
   uint32_t* counters;
 };
 
-// Tile-COO groups loaded with a tile, one per lane: at 1 % outliers a 128 x 64
-// tile holds about 21 groups in the default packing (47 by column), so one
-// 64-group load covers it; the rare larger tiles load the rest in the tile's
-// compute.  Every load instruction a tile issues costs time whatever its
-// size, so a tile issues as few as it can.
-constexpr int kGroupLoads = 1;
+// Tile-COO groups loaded with a tile, GL loads of one per lane: at 1 %
+// outliers a 128 x 64 tile holds about 21 groups in the default packing (47 by
+// column), so one 64-group load covers it.  Every load instruction a tile
+// issues costs time whatever its size, so the second one (GL = 2) is only for
+// matrices whose tiles often hold more than 64 groups; groups past 64 GL are
+// loaded in the tile's compute, which then waits for every load in flight.
 
 // Global loads one tile costs in each mode (each counts once in vmcnt).  With
 // BK the scales and zero-points of all of a wave's tiles are loaded once,
 // before its first tile.
-template <int MB, int MODE, bool DENSE, bool SPARSE, int XR, bool BK>
+template <int MB, int MODE, bool DENSE, bool SPARSE, int XR, bool BK, int GL>
 constexpr int loads_per_tile() {
   return (DENSE ? (BK ? 4 : 6) : 0) + (MODE == 0 ? 1 : XR > 0 ? XR : 4 * MB) +
-         (SPARSE ? kGroupLoads : 0);
+         (SPARSE ? GL : 0);
 }
 
 // Tiles in flight per wave.  Each buffer is one more copy of the tile code
@@ -201,7 +202,7 @@ template <> struct StripVec<2> { typedef uint2 words; typedef uint32_t scales; }
 template <> struct StripVec<4> { typedef uint4 words; typedef uint2 scales; };
 
 // Everything one wave needs for one tile, held in registers until used.
-template <int MB, int MODE, int NCB>
+template <int MB, int MODE, int NCB, int GL>
 struct TileRegs {
   static constexpr int NX = MODE == 0 ? 1 : 4 * MB;
   typename StripVec<NCB>::words w[4];   // codes: rows 16t + 4*step + h, columns n0 + NCB*c4 .. + NCB-1
@@ -209,7 +210,7 @@ struct TileRegs {
   uint32_t z;      // zero-point word holding those columns
   uint4 x[NX];     // MODE 0: X chunk lane (row lane/16, elements 8*(lane%16)..+7)
                    // MODE 1: A fragment [mb][step]: row 16mb + c4, elements 32step + 8h..+7
-  uint4 g[kGroupLoads];   // Tile-COO group lane (+ 64 j) of the tile
+  uint4 g[GL];     // Tile-COO group lane (+ 64 j) of the tile
   uint32_t g0, g1; // the tile's group range
 };
 
@@ -238,9 +239,9 @@ struct Operands {
 // counts outstanding loads exactly across the prefetch.  A wave-wide load of
 // one step covers 4 packed rows x (16 NCB) columns: 128-byte row segments for
 // 32-column strips, 256-byte ones for 64-column strips.
-template <int MB, int MODE, int NCB, bool DENSE, int XR, bool BK>
+template <int MB, int MODE, int NCB, bool DENSE, int XR, bool BK, int GL>
 __device__ __forceinline__ void load_tile_dense(const MatmulArgs& a, const Operands<MB>& op,
-                                                int t, int n0, TileRegs<MB, MODE, NCB>& r) {
+                                                int t, int n0, TileRegs<MB, MODE, NCB, GL>& r) {
   if (DENSE) {
     const uint32_t step_bytes = uint32_t(a.N) * 16u;   // 4 rows of packed words = 32 k
     const uint32_t wt = (uint32_t(t) * 16u * uint32_t(a.N) + uint32_t(n0)) * 4u;
@@ -270,10 +271,10 @@ __device__ __forceinline__ void load_tile_dense(const MatmulArgs& a, const Opera
   }
 }
 
-// The tile's first 64 kGroupLoads Tile-COO groups, one per lane and pass.
-template <int MB, int MODE, int NCB, bool SPARSE>
+// The tile's first 64 GL Tile-COO groups, one per lane and pass.
+template <int MB, int MODE, int NCB, bool SPARSE, int GL>
 __device__ __forceinline__ void load_tile_sparse(const Operands<MB>& op, int lane, uint32_t g0,
-                                                 uint32_t g1, TileRegs<MB, MODE, NCB>& r) {
+                                                 uint32_t g1, TileRegs<MB, MODE, NCB, GL>& r) {
   if (SPARSE) {
     r.g0 = g0;
     r.g1 = g1;
@@ -282,7 +283,7 @@ __device__ __forceinline__ void load_tile_sparse(const Operands<MB>& op, int lan
     // with no outliers at all `packed` points at valid scratch.
     const uint32_t last = g1 > g0 ? g1 - 1 - g0 : 0u;
 #pragma unroll
-    for (int j = 0; j < kGroupLoads; ++j)
+    for (int j = 0; j < GL; ++j)
       r.g[j] = buf_load16(op.g, min(uint32_t(lane + 64 * j), last) * 16u, g0 * 16u);
   }
 }
@@ -429,7 +430,7 @@ __device__ __forceinline__ void sparse_gather(const MatmulArgs& a, const uint16_
 // SIMD (half the register file), which every instance launched fits without
 // spilling.
 template <int MB, int MODE, int NCB, bool KD, bool KS, int NW, bool SK, int NWS, int XR, bool BK,
-          bool DV>
+          bool DV, int GL>
 __global__ void __launch_bounds__(64 * (NW + NWS))
     __attribute__((amdgpu_waves_per_eu(MB == 2 ? 2 : 1))) matmul_kernel(
         const uint32_t* Wq, const uint16_t* scales, const uint32_t* zeros, const uint16_t* X,
@@ -612,21 +613,21 @@ __global__ void __launch_bounds__(64 * (NW + NWS))
   auto tiles = [&](auto rd_c, auto rs_c) __attribute__((always_inline)) {
     constexpr bool DENSE = decltype(rd_c)::value;
     constexpr bool SPARSE = decltype(rs_c)::value;
-    auto issue_sparse = [&](int t, TileRegs<MB, MODE, NCB>& r) __attribute__((always_inline)) {
+    auto issue_sparse = [&](int t, TileRegs<MB, MODE, NCB, GL>& r) __attribute__((always_inline)) {
       uint32_t g0 = 0, g1 = 0;
       if (SPARSE) {
         const uint32_t ng = uint32_t(a.n_groups);   // < 2^27, checked on the host
         g0 = min(uint32_t(__builtin_amdgcn_readlane(int(tp), t - w_lo)), ng);
         g1 = max(g0, min(uint32_t(__builtin_amdgcn_readlane(int(tp), t - w_lo + 1)), ng));
       }
-      load_tile_sparse<MB, MODE, NCB, SPARSE>(op, lane, g0, g1, r);
+      load_tile_sparse<MB, MODE, NCB, SPARSE, GL>(op, lane, g0, g1, r);
     };
-    auto issue = [&](int t, TileRegs<MB, MODE, NCB>& r) __attribute__((always_inline)) {
-      load_tile_dense<MB, MODE, NCB, DENSE, XR, BK>(a, op, t, n0, r);
+    auto issue = [&](int t, TileRegs<MB, MODE, NCB, GL>& r) __attribute__((always_inline)) {
+      load_tile_dense<MB, MODE, NCB, DENSE, XR, BK, GL>(a, op, t, n0, r);
       issue_sparse(t, r);
     };
 
-    auto compute = [&](const TileRegs<MB, MODE, NCB>& cur, int tt) __attribute__((always_inline)) {
+    auto compute = [&](const TileRegs<MB, MODE, NCB, GL>& cur, int tt) __attribute__((always_inline)) {
       // ---- X fragments
       bf16x8_t A[MB][4];
       if (MODE == 0) {
@@ -775,18 +776,30 @@ __global__ void __launch_bounds__(64 * (NW + NWS))
       // image, read it back per step and multiply into the output tile.
       // Every lane scatters (and later clears): lanes past the tile's last
       // group hold that group again and rewrite the same values at the same
-      // places, so only an empty tile (whose loaded group is not its own)
-      // is skipped -- a wave-uniform branch, no per-lane masking.
+      // places; the loaded group of an empty tile is not its own and goes to
+      // the trash word.  The one branch is to the tiles of more than 64 GL
+      // groups.
       uint32_t n_g = 0;
       if (SPARSE) n_g = cur.g1 - cur.g0;
-      uint32_t addr[kGroupLoads][4];
+      uint32_t addr[GL][4];
       if (SPM) {
   #pragma unroll
-        for (int j = 0; j < kGroupLoads; ++j)
-          if (n_g > 64u * j) scatter_group<NCB, kFastAddr>(img_a, trash, cur.g[j], half, addr[j]);
-        for (uint32_t gi = 64 * kGroupLoads + lane; gi < n_g; gi += 64) {
-          uint32_t ad[4];
-          scatter_group<NCB, kFastAddr>(img_a, trash, a.packed[cur.g0 + gi], half, ad);
+        for (int j = 0; j < GL; ++j)
+          scatter_group<NCB, kFastAddr>(img_a, trash, cur.g[j], half, uint32_t(-int(n_g) >> 31), addr[j]);
+        if (__builtin_expect(n_g > 64u * GL, 0)) {
+          // four passes' loads at once, past the end the last group again
+          for (uint32_t base = 64 * GL; base < n_g; base += 256) {
+            uint4 more[4];
+  #pragma unroll
+            for (int j = 0; j < 4; ++j)
+              more[j] = buf_load16(op.g, min(base + 64u * j + lane, n_g - 1) * 16u, cur.g0 * 16u);
+  #pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              uint32_t ad[4];
+              if (base + 64u * j < n_g)
+                scatter_group<NCB, kFastAddr>(img_a, trash, more[j], half, 0xFFFFFFFFu, ad);
+            }
+          }
         }
         __builtin_amdgcn_wave_barrier();
         const uint4* b4 = reinterpret_cast<const uint4*>(bo);
@@ -823,11 +836,11 @@ __global__ void __launch_bounds__(64 * (NW + NWS))
       }
 
       // ---- gather mapping: the first two groups' X values from the staged slice
-      Gathered gx[kGroupLoads];
-      bool gsingle[kGroupLoads] = {};
+      Gathered gx[GL];
+      bool gsingle[GL] = {};
       if (SPARSE && MODE == 0) {
   #pragma unroll
-        for (int j = 0; j < kGroupLoads; ++j) {
+        for (int j = 0; j < GL; ++j) {
           gsingle[j] = uint32_t(lane + 64 * j) < n_g && single_column(decode_group(cur.g[j]));
           if (gsingle[j]) gather_x(a, xs, cur.g[j], gx[j]);
         }
@@ -837,23 +850,21 @@ __global__ void __launch_bounds__(64 * (NW + NWS))
       if (SPM) {
         __builtin_amdgcn_wave_barrier();
   #pragma unroll
-        for (int j = 0; j < kGroupLoads; ++j)
-          if (n_g > 64u * j) clear_group(addr[j]);
-        for (uint32_t gi = 64 * kGroupLoads + lane; gi < n_g; gi += 64) {
-          const uint4 raw = a.packed[cur.g0 + gi];
-          uint32_t ad[4];
-          group_addresses<NCB, kFastAddr>(img_a, raw.x, raw.y, ad);
-          clear_group(ad);   // zeros everywhere the group could have written
+        for (int j = 0; j < GL; ++j) clear_group(addr[j]);
+        if (__builtin_expect(n_g > 64u * GL, 0)) {
+          uint4* b4 = reinterpret_cast<uint4*>(bo);
+  #pragma unroll
+          for (int i = 0; i < kImageBlocks; ++i) b4[i * 64 + lane] = uint4{0u, 0u, 0u, 0u};
         }
       }
       // ---- gather mapping: finish the first two groups, then any further ones
       if (SPARSE && MODE == 0) {
   #pragma unroll
-        for (int j = 0; j < kGroupLoads; ++j) {
+        for (int j = 0; j < GL; ++j) {
           if (gsingle[j]) gather_add(a, cur.g[j], gx[j], shc);
           else if (uint32_t(lane + 64 * j) < n_g) sparse_gather(a, xs, cur.g[j], shc);
         }
-        for (uint32_t gi = 64 * kGroupLoads + lane; gi < n_g; gi += 64)
+        for (uint32_t gi = 64 * GL + lane; gi < n_g; gi += 64)
           sparse_gather(a, xs, a.packed[cur.g0 + gi], shc);
       }
       __builtin_amdgcn_wave_barrier();
@@ -870,9 +881,9 @@ __global__ void __launch_bounds__(64 * (NW + NWS))
     // tile_indptr, while its dense loads are already out.
     // The loop body holds one copy of the tile code per register buffer; the
     // last partial round is predicated, not peeled.
-    constexpr int NL = loads_per_tile<MB, MODE, DENSE, SPARSE, XR, BK && DENSE>();
+    constexpr int NL = loads_per_tile<MB, MODE, DENSE, SPARSE, XR, BK && DENSE, GL>();
     constexpr int D = pipeline_depth<MB, NCB>();
-    TileRegs<MB, MODE, NCB> rg[D];
+    TileRegs<MB, MODE, NCB, GL> rg[D];
     if (w_lo < w_hi) {
       const int last = w_hi - 1;
       // With BK the scales and zero-points of every tile of the wave go out
@@ -886,7 +897,7 @@ __global__ void __launch_bounds__(64 * (NW + NWS))
       }
 #pragma unroll
       for (int i = 0; i < D; ++i) {
-        load_tile_dense<MB, MODE, NCB, DENSE, XR, BK>(a, op, min(w_lo + i, last), n0, rg[i]);
+        load_tile_dense<MB, MODE, NCB, DENSE, XR, BK, GL>(a, op, min(w_lo + i, last), n0, rg[i]);
         __builtin_amdgcn_sched_barrier(0);
       }
       if (SPARSE) {
@@ -1141,9 +1152,9 @@ __global__ void __launch_bounds__(256) decode_kernel(const uint32_t* tile_indptr
 }
 
 template <int MB, int MODE, int NCB, bool DENSE, bool SPARSE, int NW, bool SK, int NWS, int XR,
-          bool BK, bool DV = false>
+          bool BK, bool DV = false, int GL = 1>
 int launch_variant(const fqi::Plan& pl, const MatmulArgs& args, hipStream_t stream) {
-  auto kern = matmul_kernel<MB, MODE, NCB, DENSE, SPARSE, NW, SK, NWS, XR, BK, DV>;
+  auto kern = matmul_kernel<MB, MODE, NCB, DENSE, SPARSE, NW, SK, NWS, XR, BK, DV, GL>;
   // the layout of this instance (with no outliers the fused launch drops its
   // sparse half, whose layout is never larger than the plan's)
   const uint32_t lds = lds_layout(MODE, NCB, NW, NWS, XR, SPARSE, pl.slab_M).lds_bytes;
@@ -1182,6 +1193,10 @@ int launch_roles_bk(const fqi::Plan& pl, const MatmulArgs& a, bool dense, bool s
   if constexpr (MODE == 1 && !SK && !(NCB == 4 && MB == 2 && NW == 8) && XR < 6) {
     if (dense && sparse && pl.NWS > 0)
       return launch_variant<MB, MODE, NCB, true, true, NW, SK, NW / 2, XR, BK>(pl, a, s);
+  }
+  if constexpr (MODE == 1 && !SK) {
+    if (dense && sparse && a.two_group_loads)
+      return launch_variant<MB, MODE, NCB, true, true, NW, SK, 0, XR, BK, false, 2>(pl, a, s);
   }
   if (dense && sparse) return launch_variant<MB, MODE, NCB, true, true, NW, SK, 0, XR, BK>(pl, a, s);
   if (dense) return launch_variant<MB, MODE, NCB, true, false, NW, SK, 0, XR, BK>(pl, a, s);
@@ -1365,7 +1380,6 @@ Shape default_shape(int T, int N, int n_slabs, int slab_M) {
 
 bool make_plan(int M, int K, int N, int split_k, bool dense, bool sparse, int B,
                int64_t max_tile_groups, Plan* pl, int mode, int opts) {
-  (void)max_tile_groups;
   if (M < 1 || M > kMaxM || K < kTileK || N < kTileN || K % kTileK || N % kTileN) return false;
   if (N / kTileN > kMaxStrips) return false;
   if (sparse && (B < 1 || B > kMaxBuckets)) return false;
@@ -1384,6 +1398,7 @@ bool make_plan(int M, int K, int N, int split_k, bool dense, bool sparse, int B,
   p.slab_M = std::min(M, kSlabM);
   p.MB = p.slab_M <= 16 ? 1 : 2;
   p.T = K / kTileK;
+  p.max_tile_groups = max_tile_groups;
   // strip width: forced, or 64 for the gather mapping and Stream-K, or the
   // measured default
   const bool forced = (opts & (kOptStrip32 | kOptStrip64 | kOptStreamK)) || mode == 0;
@@ -1533,6 +1548,12 @@ int launch_matmul(const Plan& pl, const MatmulPtrs& p, bool dense, bool sparse, 
   a.G = pl.G;
   a.C = pl.C;
   a.n_slabs = pl.n_slabs;
+  // A second group load per tile where some tile needs it and the average tile
+  // is half way there: 4096 x 14336 at 8 rows, 5 % outliers 17.3 -> 14.8 us (103
+  // groups a tile), half of them in 2 % of the columns 23.0 -> 20.1; at 2 %,
+  // whose tiles hold at most 54, one load (13.2 us).
+  const int64_t tiles = int64_t(pl.T) * (pl.N / kTileN);
+  a.two_group_loads = pl.max_tile_groups > 64 && p.n_groups >= 32 * tiles;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (sparse && p.n_groups == 0) {
     // No outliers: the fused launch drops its sparse half; a sparse-only
@@ -1541,7 +1562,7 @@ int launch_matmul(const Plan& pl, const MatmulPtrs& p, bool dense, bool sparse, 
     if (dense) sparse = false;
     else a.packed = reinterpret_cast<const uint4*>(p.workspace);
   }
-  if (pl.rows_RB && dense && !p.y_addend) return launch_rows(pl, p, sparse, stream);
+  if (pl.rows_RB && dense && !p.y_addend) return launch_rows(pl, p, sparse, a.two_group_loads, stream);
   if (pl.MODE == 0) return fqk::launch_mode<1, 0>(pl, a, dense, sparse, s);
   if (pl.MB == 1) return fqk::launch_mode<1, 1>(pl, a, dense, sparse, s);
   return fqk::launch_mode<2, 1>(pl, a, dense, sparse, s);

@@ -42,6 +42,8 @@
 //   4096 x 14336  128 rows 47.2 -> 34.2 us, 64 rows 27.7 -> 23.5, 40 rows 27.0 -> 23.7
 //   14336 x 4096  128 rows 40.6 -> 35.1 us, 64 rows 27.6 -> 26.0
 //   4096 x 6144   128 rows 26.0 -> 22.8 us
+// With two group loads per tile (5 % outliers): 4096 x 14336 at 128 rows
+// 58.0 -> 39.8 us, at 64 rows 33.4 -> 27.1.
 // Tried and slower (4096 x 14336 at 128 rows, 34.1 us): 16x16x32 MFMAs 38.2 us
 // with scalar-unit masks in the scatter; tile_indptr by scalar loads, which every
 // LDS wait then waits for, 39.0 us; all loads and the scatter's addresses among
@@ -152,7 +154,7 @@ __device__ __forceinline__ void rows_places(uint32_t page, uint32_t base_rep, ui
   addr[3] = __builtin_amdgcn_perm(page, a23, 0x07060302u);
 }
 
-template <int RB, bool SPARSE>
+template <int RB, bool SPARSE, int GL>
 __global__ void __launch_bounds__(64 * kCW * kKG) __attribute__((amdgpu_waves_per_eu(2)))
 rows_kernel(const uint32_t* Wq, const uint16_t* scales, const uint32_t* zeros, const uint16_t* X,
             const uint32_t* tile_indptr, int M_all, int K, int N, int GS, RowsTail tail) {
@@ -266,32 +268,40 @@ rows_kernel(const uint32_t* Wq, const uint16_t* scales, const uint32_t* zeros, c
     tp = tile_indptr[uint32_t(n0 >> 6) * uint32_t(T) + uint32_t(w_lo + min(lane, last + 1))];
     rg = make_rsrc(tail.packed, max(ng, 1u) * 16u);
   }
-  uint4 gr{0u, 0u, 0u, 0u};
+  uint4 gr[GL] = {};               // groups lane + 64 j of a tile
   uint32_t g_lo = 0, g_n = 0;      // range of the tile whose groups are in gr
   auto load_groups = [&](int i) __attribute__((always_inline)) {
     const int t = min(i, last);
     g_lo = min(uint32_t(__builtin_amdgcn_readlane(int(tp), t)), ng);
     const uint32_t g_hi = max(g_lo, min(uint32_t(__builtin_amdgcn_readlane(int(tp), t + 1)), ng));
     g_n = i < cnt ? g_hi - g_lo : 0u;   // past the group's last tile: no groups
-    gr = buf_load16(rg, min(uint32_t(lane), g_n ? g_n - 1 : 0u) * 16u, g_lo * 16u);
+#pragma unroll
+    for (int j = 0; j < GL; ++j)
+      gr[j] = buf_load16(rg, min(uint32_t(lane + 64 * j), g_n ? g_n - 1 : 0u) * 16u, g_lo * 16u);
   };
   // The loaded groups go into the (all-zero) image in two steps: where their
-  // values go, which needs no LDS and is done among a tile's MFMAs, and the
-  // stores.  Lanes past the last group rewrite it; an empty tile's loaded
-  // group is not its own and goes to the trash word.  The only branch is the
-  // one to the rare tile of more than 64 groups.
-  uint32_t addr[4] = {0u, 0u, 0u, 0u}, next_addr[4];
-  uint32_t s_n = 0;                // what the image holds
+  // values go, which needs no LDS and is begun among a tile's MFMAs (36.7 us in
+  // one step against 34.2), and the stores.  Lanes past the last group rewrite
+  // it; an empty tile's loaded group is not its own and goes to the trash
+  // word.  The only branch is the one to the rare tile of more than
+  // 64 GL groups, whose others are loaded here.
+  uint32_t addr[GL][4] = {}, next_addr[GL][4];
+  uint32_t s_n = 0;                // groups that the image holds
   auto place = [&]() __attribute__((always_inline)) {
-    rows_places(page, img_rep, trash_rep, gr, half, g_n ? 0xFFFFFFFFu : 0u, next_addr);
+#pragma unroll
+    for (int j = 0; j < GL; ++j)
+      rows_places(page, img_rep, trash_rep, gr[j], half, g_n ? 0xFFFFFFFFu : 0u, next_addr[j]);
   };
   auto scatter = [&]() __attribute__((always_inline)) {
     s_n = g_n;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) addr[j] = next_addr[j];
-    store_group(addr, gr);
-    if (__builtin_expect(s_n > 64u, 0)) {
-      for (uint32_t g0 = 64; g0 < s_n; g0 += 64) {   // wave-uniform; the last group again past the end
+    for (int j = 0; j < GL; ++j) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) addr[j][e] = next_addr[j][e];
+      store_group(addr[j], gr[j]);
+    }
+    if (__builtin_expect(s_n > 64u * GL, 0)) {
+      for (uint32_t g0 = 64 * GL; g0 < s_n; g0 += 64) {   // the last group again past the end
         const uint4 raw = buf_load16(rg, min(g0 + lane, s_n - 1) * 16u, g_lo * 16u);
         uint32_t ad[4];
         rows_places(page, img_rep, trash_rep, raw, half, 0xFFFFFFFFu, ad);
@@ -302,8 +312,9 @@ rows_kernel(const uint32_t* Wq, const uint16_t* scales, const uint32_t* zeros, c
   // Zeros again: at the places written, or everywhere where more than one
   // pass of groups was.
   auto clear = [&]() __attribute__((always_inline)) {
-    clear_group(addr);
-    if (__builtin_expect(s_n > 64u, 0)) {
+#pragma unroll
+    for (int j = 0; j < GL; ++j) clear_group(addr[j]);
+    if (__builtin_expect(s_n > 64u * GL, 0)) {
       uint4* b4 = reinterpret_cast<uint4*>(img_p);
 #pragma unroll
       for (int i = 0; i < kRowsImage / 1024; ++i) b4[i * 64 + lane] = uint4{0u, 0u, 0u, 0u};
@@ -545,9 +556,9 @@ rows_kernel(const uint32_t* Wq, const uint16_t* scales, const uint32_t* zeros, c
   }
 }
 
-template <int RB, bool SPARSE>
+template <int RB, bool SPARSE, int GL>
 int launch_rows_variant(const fqi::Plan& pl, const fqi::MatmulPtrs& p, hipStream_t stream) {
-  auto kern = rows_kernel<RB, SPARSE>;
+  auto kern = rows_kernel<RB, SPARSE, GL>;
   constexpr int lds = RowsLds<RB>::bytes;
   static_assert(lds <= 160 * 1024, "LDS of one CU");
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -584,11 +595,16 @@ namespace fqi {
 // 4096 x 4096, 8 tiles, 17.8 against 16.8; 4096 x 6144, 16 tiles, 22.8 against
 // 26.0).  17 to 32 rows only without a split (27 rows: 4096 x 28672 27.0 against
 // 28.8 us, 4096 x 14336 split 2 18.6 against 18.5).
+// A matrix with a tile of more than kRowsMaxGroups groups is left to the strip
+// kernel, whose waves do not wait for one another at every tile (5 % outliers,
+// half in 2 % of the columns, over 200 groups in a tile: 4096 x 28672 at 27 rows
+// 67.7 against 45.6 us, 4096 x 14336 at 128 rows 70.7 against 62.7; 2 %, 100 to
+// 150 groups, at 64 rows: 26.7 against 32.1).
 // Partial sums beyond kRowsPartialLimit are left to the strip kernel, so that
 // every default launch fits the static scratch.
 void plan_rows(Plan* p) {
   p->rows_RB = 0;
-  if (p->M <= kRowsMinM) return;
+  if (p->M <= kRowsMinM || p->max_tile_groups > kRowsMaxGroups) return;
   const int rb = p->M <= 32 ? 1 : 2;
   const int blocks = (p->M + 32 * rb - 1) / (32 * rb);
   const int n_cb = (p->N + fqk::kRowsCols - 1) / fqk::kRowsCols;
@@ -607,11 +623,16 @@ void plan_rows(Plan* p) {
   p->ws_bytes = std::max(p->ws_bytes, kCounterRegion + size_t(part));
 }
 
-int launch_rows(const Plan& pl, const MatmulPtrs& p, bool sparse, void* stream) {
+int launch_rows(const Plan& pl, const MatmulPtrs& p, bool sparse, bool two_group_loads, void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (pl.rows_RB == 1)
-    return sparse ? fqk::launch_rows_variant<1, true>(pl, p, s) : fqk::launch_rows_variant<1, false>(pl, p, s);
-  return sparse ? fqk::launch_rows_variant<2, true>(pl, p, s) : fqk::launch_rows_variant<2, false>(pl, p, s);
+  if (pl.rows_RB == 1) {
+    if (!sparse) return fqk::launch_rows_variant<1, false, 1>(pl, p, s);
+    return two_group_loads ? fqk::launch_rows_variant<1, true, 2>(pl, p, s)
+                           : fqk::launch_rows_variant<1, true, 1>(pl, p, s);
+  }
+  if (!sparse) return fqk::launch_rows_variant<2, false, 1>(pl, p, s);
+  return two_group_loads ? fqk::launch_rows_variant<2, true, 2>(pl, p, s)
+                         : fqk::launch_rows_variant<2, true, 1>(pl, p, s);
 }
 
 }  // namespace fqi
