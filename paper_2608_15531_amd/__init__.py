@@ -9,6 +9,7 @@ There is no CPU fallback: if libfq.so has not been built, every call raises.
 
 from __future__ import annotations
 
+import contextlib
 import ctypes as C
 import os
 import threading
@@ -20,6 +21,7 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libfq.so")
 
 FQ_OK = 0
+_FQ_ERR_WORKSPACE = 8
 STATUS_NAMES = {0: "FQ_OK", 1: "FQ_ERR_NULL", 2: "FQ_ERR_SHAPE", 3: "FQ_ERR_RANGE",
                 4: "FQ_ERR_DUPLICATE", 5: "FQ_ERR_ZERO_VALUE", 6: "FQ_ERR_FORMAT",
                 7: "FQ_ERR_UNSUPPORTED", 8: "FQ_ERR_WORKSPACE", 9: "FQ_ERR_HIP",
@@ -122,6 +124,8 @@ EXPORTS = tuple(_SIGS)
 def load() -> C.CDLL:
     """Load libfq.so (built in-tree by build.py); raise if it is missing."""
     global _lib
+    if _lib is not None:
+        return _lib
     with _lock:
         if _lib is None:
             if not os.path.exists(LIB_PATH):
@@ -313,9 +317,15 @@ def fq_fill_padding_slots(W, qw: QuantizedWeight, host: TileCOOHost) -> int:
 
 # ---------------------------------------------------------------- device --
 
+_torch_module = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
 
 
 class TileCOODevice:
@@ -365,14 +375,36 @@ def workspace(nbytes: int, device, stream_handle: int):
     return buf
 
 
+_NO_STREAM = contextlib.nullcontext()
+
+
 def _on_stream(stream):
     """Makes `stream` current while Y and the workspace are allocated, so the
     caching allocator ties them to the stream the kernel runs on and the
     workspace's zero fill precedes the kernel there."""
-    import contextlib
     if stream is None:
-        return contextlib.nullcontext()
+        return _NO_STREAM
     return _torch().cuda.stream(stream)
+
+
+def _launch(call, sizer, pr, ws, device, stream, where):
+    """call(workspace tensor, stream handle) -> status.  Without a workspace from
+    the caller the one kept for the stream is tried first; the library checks its
+    size against the launch before it enqueues anything, and only when that check
+    fails (or none is kept yet) is the size asked for and a larger one made."""
+    sh = _stream_handle(stream, device)
+    if ws is None:
+        ws = _workspaces.get((device.index, sh))
+        if ws is not None:
+            status = call(ws, sh)
+            if status != _FQ_ERR_WORKSPACE:
+                _check(status, where)
+                return
+        need = C.c_size_t(0)
+        _check(sizer(C.byref(pr), C.byref(need)), sizer.__name__)
+        with _on_stream(stream):
+            ws = workspace(need.value, device, sh)
+    _check(call(ws, sh), where)
 
 
 def _problem(M, K, N, y_dtype, split_k, group=128, sparse="auto", flags=0) -> fq_problem:
@@ -380,10 +412,9 @@ def _problem(M, K, N, y_dtype, split_k, group=128, sparse="auto", flags=0) -> fq
 
 
 def _check_tensor(t, dtype, shape, name):
-    torch = _torch()
-    if not isinstance(t, torch.Tensor) or not t.is_cuda:
+    if not isinstance(t, _torch().Tensor) or not t.is_cuda:
         raise TypeError(f"{name} must be a CUDA (HIP) tensor")
-    if t.dtype != dtype or tuple(t.shape) != tuple(shape) or not t.is_contiguous():
+    if t.dtype != dtype or t.shape != shape or not t.is_contiguous():
         raise ValueError(f"{name}: expected contiguous {dtype} {tuple(shape)}, got "
                          f"{t.dtype} {tuple(t.shape)}")
 
@@ -413,17 +444,12 @@ def fq_w4a16_outlier_matmul(X, Wq, scales, zeros, tc: TileCOODevice, Y=None, y_d
     lib = load()
     with _on_stream(stream):
         M, K, N, ydt, Y = _matmul_args(X, Wq, scales, zeros, Y, y_dtype, group)
-        pr = _problem(M, K, N, ydt, split_k, group, sparse, flags)
-        need = C.c_size_t(0)
-        _check(lib.fq_workspace_bytes(C.byref(pr), C.byref(need)), "fq_workspace_bytes")
-        sh = _stream_handle(stream, X.device)
-        if ws is None:
-            ws = workspace(need.value, X.device, sh)
+    pr = _problem(M, K, N, ydt, split_k, group, sparse, flags)
     tcs = tc.struct()
-    _check(lib.fq_w4a16_outlier_matmul(C.byref(pr), X.data_ptr(), Wq.data_ptr(),
-                                       scales.data_ptr(), zeros.data_ptr(), C.byref(tcs),
-                                       Y.data_ptr(), ws.data_ptr(), ws.numel(), sh),
-           "fq_w4a16_outlier_matmul")
+    _launch(lambda w, sh: lib.fq_w4a16_outlier_matmul(
+                C.byref(pr), X.data_ptr(), Wq.data_ptr(), scales.data_ptr(), zeros.data_ptr(),
+                C.byref(tcs), Y.data_ptr(), w.data_ptr(), w.numel(), sh),
+            lib.fq_workspace_bytes, pr, ws, X.device, stream, "fq_w4a16_outlier_matmul")
     return Y
 
 
@@ -454,19 +480,13 @@ def fq_w4a16_outlier_matmul_unfused(X, Wq, scales, zeros, tc: TileCOODevice, Y=N
     lib = load()
     with _on_stream(stream):
         M, K, N, ydt, Y = _matmul_args(X, Wq, scales, zeros, Y, y_dtype, group)
-        pr = _problem(M, K, N, ydt, split_k, group, sparse, flags)
-        need = C.c_size_t(0)
-        _check(lib.fq_workspace_bytes_unfused(C.byref(pr), C.byref(need)),
-               "fq_workspace_bytes_unfused")
-        sh = _stream_handle(stream, X.device)
-        if ws is None:
-            ws = workspace(need.value, X.device, sh)
+    pr = _problem(M, K, N, ydt, split_k, group, sparse, flags)
     tcs = tc.struct()
-    _check(lib.fq_w4a16_outlier_matmul_unfused(C.byref(pr), X.data_ptr(), Wq.data_ptr(),
-                                               scales.data_ptr(), zeros.data_ptr(),
-                                               C.byref(tcs), Y.data_ptr(), ws.data_ptr(),
-                                               ws.numel(), sh),
-           "fq_w4a16_outlier_matmul_unfused")
+    _launch(lambda w, sh: lib.fq_w4a16_outlier_matmul_unfused(
+                C.byref(pr), X.data_ptr(), Wq.data_ptr(), scales.data_ptr(), zeros.data_ptr(),
+                C.byref(tcs), Y.data_ptr(), w.data_ptr(), w.numel(), sh),
+            lib.fq_workspace_bytes_unfused, pr, ws, X.device, stream,
+            "fq_w4a16_outlier_matmul_unfused")
     return Y
 
 
@@ -476,15 +496,11 @@ def fq_w4a16_matmul(X, Wq, scales, zeros, Y=None, y_dtype="bf16", split_k: int =
     lib = load()
     with _on_stream(stream):
         M, K, N, ydt, Y = _matmul_args(X, Wq, scales, zeros, Y, y_dtype, group)
-        pr = _problem(M, K, N, ydt, split_k, group, flags=flags)
-        need = C.c_size_t(0)
-        _check(lib.fq_workspace_bytes(C.byref(pr), C.byref(need)), "fq_workspace_bytes")
-        sh = _stream_handle(stream, X.device)
-        if ws is None:
-            ws = workspace(need.value, X.device, sh)
-    _check(lib.fq_w4a16_matmul(C.byref(pr), X.data_ptr(), Wq.data_ptr(), scales.data_ptr(),
-                               zeros.data_ptr(), Y.data_ptr(), ws.data_ptr(), ws.numel(), sh),
-           "fq_w4a16_matmul")
+    pr = _problem(M, K, N, ydt, split_k, group, flags=flags)
+    _launch(lambda w, sh: lib.fq_w4a16_matmul(
+                C.byref(pr), X.data_ptr(), Wq.data_ptr(), scales.data_ptr(), zeros.data_ptr(),
+                Y.data_ptr(), w.data_ptr(), w.numel(), sh),
+            lib.fq_workspace_bytes, pr, ws, X.device, stream, "fq_w4a16_matmul")
     return Y
 
 
