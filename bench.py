@@ -53,11 +53,27 @@ GEMM_CANDIDATES = 16
 GEMM_WORKSPACE = 64 << 20
 
 
+def rows_kernel_runs(M, K, N):
+    """Whether the row-block kernel takes the call (its planner's rule, for
+    matrices without very full tiles): more than 16 rows and at least 14 tiles
+    of K per workgroup of 128 columns x 64 (32) rows; no split up to 32 rows."""
+    if M <= 16:
+        return False
+    rows = 32 if M <= 32 else 64
+    units = -(-N // 128) * -(-M // rows)
+    split = max(1, 256 // units)
+    if rows == 32 and split > 1:
+        return False
+    return K // 128 // max(split, -(-(K // 128) // 126)) >= 14
+
+
 def kernel_name(fq, M, K, N, packing=None, flags=0):
     """Template instance of the fused kernel the library launches for (M, K, N),
     a Tile-COO packed with `packing` (default: the library default) and the
     switches `flags`."""
     packing = packing or {}
+    if not flags and rows_kernel_runs(M, K, N):
+        return f"rows_kernel<{1 if M <= 32 else 2}, true, 1>"
     c = fq.fq_launch_config(M, K, N, buckets_per_tile=packing.get("buckets_per_tile"),
                             group_mode=packing.get("group_mode"), flags=flags)
     mb = 1 if min(M, 32) <= 16 else 2
@@ -281,7 +297,7 @@ def kernel_source_digest():
     import hashlib
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_2608_15531_amd", "csrc")
-    for f in ("kernels.hip", "device.hpp", "internal.hpp"):
+    for f in ("kernels.hip", "rows.hip", "device.hpp", "internal.hpp"):
         with open(os.path.join(csrc, f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()
@@ -704,7 +720,7 @@ def trace_summary(stats_csv, traced_log, plain_log):
            "reordered through LDS (ceil(M/4); 0 = loads in operand order); BK scales and "
            "zero-points loaded once per wave; DV dense products by VALU dot products "
            "(ablation); GL loads of 64 outlier groups per tile.", "",
-           f"Kernel sources sha256 (kernels.hip, device.hpp, internal.hpp): "
+           f"Kernel sources sha256 (kernels.hip, rows.hip, device.hpp, internal.hpp): "
            f"`{kernel_source_digest()}`", "",
            "| kernel | launches (shapes, default packing) | calls | total ns | average ns | min ns "
            "| max ns |", "|---|---|---|---|---|---|---|"]
@@ -1536,7 +1552,7 @@ def trace_unfused_summary(trace_csv, log_path):
            "warm-up replays and the capture's warm-up call (not counted), over the rotated "
            "weight copies.  `unfused sum` = median over launches of the two kernels' durations "
            "added; the benchmark's `unfused_us` is the event-timed pair (dispatch gaps "
-           "included).  Kernel sources sha256 (kernels.hip, device.hpp, internal.hpp): "
+           "included).  Kernel sources sha256 (kernels.hip, rows.hip, device.hpp, internal.hpp): "
            f"`{kernel_source_digest()}`", "",
            "| matmul | fused us | unfused dense us | unfused SpMM us | unfused sum us | "
            "unfused sum / fused |", "|---|---|---|---|---|---|"]
@@ -1599,7 +1615,7 @@ def trace_per_matmul(trace_csv, log_path):
            f"{TRACE_WARM} warm-up replays and the capture's warm-up call (not counted).  "
            "Tile-COO: the library default packing (by-bucket groups, one bucket per tile).  "
            "`frac` = algorithmic bytes / median kernel duration / 8 TB/s.", "",
-           f"Kernel sources sha256 (kernels.hip, device.hpp, internal.hpp): "
+           f"Kernel sources sha256 (kernels.hip, rows.hip, device.hpp, internal.hpp): "
            f"`{kernel_source_digest()}`", "",
            "| matmul | kernel | launches | median us | mean us | bytes | GB/s (median) | frac |",
            "|---|---|---|---|---|---|---|---|"]

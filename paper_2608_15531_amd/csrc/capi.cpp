@@ -87,6 +87,11 @@ fq_status run(const fq_problem* pr, const uint16_t* X, const uint32_t* Wq,
   fqi::Plan plan;
   if (!plan_for(pr, tc, dense, sparse, &plan)) return FQ_ERR_UNSUPPORTED;
   if (!workspace) return FQ_ERR_WORKSPACE;
+  // a workspace that holds the strip kernel's partial sums only: that kernel
+  if (workspace_bytes < plan.ws_bytes && workspace_bytes >= plan.strip_ws_bytes) {
+    plan.rows_RB = 0;
+    plan.ws_bytes = plan.strip_ws_bytes;
+  }
   if (workspace_bytes < plan.ws_bytes || !aligned(workspace, 256)) return FQ_ERR_WORKSPACE;
   fqi::MatmulPtrs p{};
   p.X = X;

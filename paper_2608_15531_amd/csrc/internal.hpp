@@ -61,7 +61,8 @@ struct Plan {
   // image), then the gather-mode sparse output buffers or the X stages
   size_t slot_bytes, off_shc, off_flag, off_trash, off_xs, lds_bytes;
   // workspace layout, bytes: counters at 0, partial sums at kCounterRegion
-  size_t partial_bytes, ws_bytes;
+  // (ws_bytes: of whichever kernel runs; strip_ws_bytes: of the strip kernel)
+  size_t partial_bytes, ws_bytes, strip_ws_bytes;
   // the row-block kernel's launch (rows.hip), where it is the one to run:
   // 32-row blocks per workgroup (0: the strip kernel runs), row blocks of M,
   // K ranges and workgroups per row block

@@ -1523,7 +1523,7 @@ bool make_plan(int M, int K, int N, int split_k, bool dense, bool sparse, int B,
   // every array is addressed with 32-bit byte offsets
   const size_t lim = size_t(1) << 31;
   if (size_t(K) * N / 2 >= lim || size_t(M) * K * 2 >= lim || p.partial_bytes >= lim) return false;
-  p.ws_bytes = kCounterRegion + align_up(p.partial_bytes, 256);
+  p.ws_bytes = p.strip_ws_bytes = kCounterRegion + align_up(p.partial_bytes, 256);
   if (dense && split_k == 0 && opts == 0 && mode != 0) plan_rows(&p);
   *pl = p;
   return true;

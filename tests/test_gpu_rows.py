@@ -80,3 +80,19 @@ def test_rows_kernel_graph_replays(gpu_lib):
         other = fq.fq_w4a16_outlier_matmul(X, Wq, s, z, tc, y_dtype="f32", ws=ws)
         torch.cuda.synchronize()
         assert torch.equal(other, eager)
+
+
+def test_rows_kernel_small_workspace(gpu_lib):
+    """A workspace without room for the row-block kernel's partial sums, but
+    large enough for the strip kernel's launch, is served by the strip kernel."""
+    fq = gpu_lib
+    M, K, N = 64, 7296, 8192
+    p = make_exact_problem(M, K, N, frac=0.01, seed=4)
+    X, Wq, s, z = fq.to_device(p)
+    tc = fq.TileCOODevice(fq.fq_pack_tile_coo(K, N, p.k, p.n, p.v))
+    assert fq.fq_workspace_bytes(M, K, N) > 256 * 1024
+    small = torch.zeros(256 * 1024, dtype=torch.uint8, device="cuda")   # 64-column strips need no split here
+    y = fq.fq_w4a16_outlier_matmul(X, Wq, s, z, tc, y_dtype="f32")
+    y_small = fq.fq_w4a16_outlier_matmul(X, Wq, s, z, tc, y_dtype="f32", ws=small)
+    torch.cuda.synchronize()
+    assert torch.equal(y, y_small)
