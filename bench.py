@@ -56,7 +56,8 @@ GEMM_WORKSPACE = 64 << 20
 def rows_kernel_runs(M, K, N):
     """Whether the row-block kernel takes the call (its planner's rule, for
     matrices without very full tiles): more than 16 rows and at least 14 tiles
-    of K per workgroup of 128 columns x 64 (32) rows; no split up to 32 rows."""
+    of K per workgroup of 128 columns x 64 (32) rows; no split up to 32 rows;
+    rounds of workgroups filled."""
     if M <= 16:
         return False
     rows = 32 if M <= 32 else 64
@@ -64,7 +65,13 @@ def rows_kernel_runs(M, K, N):
     split = max(1, 256 // units)
     if rows == 32 and split > 1:
         return False
-    return K // 128 // max(split, -(-(K // 128) // 126)) >= 14
+    split = max(split, -(-(K // 128) // 126))
+    rounds = -(-units * split // 256)
+    if rounds > 1 and rows == 32:
+        return False
+    if rounds > 1 and units * split / (256 * rounds) * M / (rows * -(-M // rows)) < 0.65:
+        return False
+    return K // 128 // split >= 14
 
 
 def kernel_name(fq, M, K, N, packing=None, flags=0):

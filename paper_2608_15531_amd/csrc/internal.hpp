@@ -31,6 +31,7 @@ constexpr size_t kScratchBytes = kCounterRegion + (size_t(8) << 20);
 // many tiles per workgroup and partial sums that the static scratch holds.
 constexpr int kRowsMinM = 16;
 constexpr int kRowsMinTiles = 14;
+constexpr double kRowsMinFill = 0.65; // of the rounds of workgroups, with more than one
 constexpr int kRowsMaxGroups = 160;   // of the largest tile
 constexpr size_t kRowsPartialLimit = kScratchBytes - kCounterRegion;
 

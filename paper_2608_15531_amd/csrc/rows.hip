@@ -600,6 +600,12 @@ namespace fqi {
 // half in 2 % of the columns, over 200 groups in a tile: 4096 x 28672 at 27 rows
 // 67.7 against 45.6 us, 4096 x 14336 at 128 rows 70.7 against 62.7; 2 %, 100 to
 // 150 groups, at 64 rows: 26.7 against 32.1).
+// More than one round of workgroups has to be filled, in CUs and rows together, by
+// kRowsMinFill (4096 x 38400 at 64 rows, 300 workgroups, 0.59: 68.9 against 62.6 us;
+// 4096 x 28672 at 80 rows, 0.55: 67.6 against 67.7, at 128 rows, 0.88: 68.1 against
+// 79.8).  A single round that leaves CUs idle still gains (4096 x 16512 at 64 rows,
+// 129 workgroups, 33.2 against 37.9); with 17 to 32 rows only a single round does
+// (8192 x 57344 at 32 rows 98.4 against 97.2).
 // Partial sums beyond kRowsPartialLimit are left to the strip kernel, so that
 // every default launch fits the static scratch.
 void plan_rows(Plan* p) {
@@ -613,6 +619,10 @@ void plan_rows(Plan* p) {
   if (rb == 1 && S > 1) return;
   S = std::max(S, (p->T + 125) / 126);   // at most 63 tiles per K group
   if (p->T / S < kRowsMinTiles) return;
+  // one workgroup runs per CU: rounds of 256
+  const int64_t wgs = units * S, rounds = (wgs + 255) / 256;
+  if (rounds > 1 && rb == 1) return;
+  if (rounds > 1 && double(wgs) / double(256 * rounds) * p->M / (32 * rb * blocks) < kRowsMinFill) return;
   const int64_t part = S > 1 ? units * S * fqk::kCW * rb * 4 * 1024 : 0;
   if (part > int64_t(kRowsPartialLimit)) return;
   if (int64_t(n_cb) * S >= (1 << fqk::kRowsGBits) || units > kMaxStrips) return;
