@@ -376,6 +376,7 @@ def workspace(nbytes: int, device, stream_handle: int):
 
 
 _NO_STREAM = contextlib.nullcontext()
+_STRIP_ROWS = 16   # up to so many rows, one kernel and one workspace size per problem
 
 
 def _on_stream(stream):
@@ -391,10 +392,13 @@ def _launch(call, sizer, pr, ws, device, stream, where):
     """call(workspace tensor, stream handle) -> status.  Without a workspace from
     the caller the one kept for the stream is tried first; the library checks its
     size against the launch before it enqueues anything, and only when that check
-    fails (or none is kept yet) is the size asked for and a larger one made."""
+    fails (or none is kept yet) is the size asked for and a larger one made.  With
+    more than 16 rows the size is always asked for: there a smaller workspace may
+    pass the check and get the strip kernel in the row-block kernel's place, so the
+    kernel would depend on the calls before."""
     sh = _stream_handle(stream, device)
     if ws is None:
-        ws = _workspaces.get((device.index, sh))
+        ws = _workspaces.get((device.index, sh)) if pr.M <= _STRIP_ROWS else None
         if ws is not None:
             status = call(ws, sh)
             if status != _FQ_ERR_WORKSPACE:

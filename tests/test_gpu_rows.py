@@ -11,7 +11,7 @@ import pytest
 import torch
 
 import oracle
-from synth import make_exact_problem
+from synth import make_exact_problem, make_problem
 
 pytestmark = pytest.mark.gpu
 
@@ -96,3 +96,33 @@ def test_rows_kernel_small_workspace(gpu_lib):
     y_small = fq.fq_w4a16_outlier_matmul(X, Wq, s, z, tc, y_dtype="f32", ws=small)
     torch.cuda.synchronize()
     assert torch.equal(y, y_small)
+
+
+def test_rows_kernel_kept_workspace_grows(gpu_lib):
+    """The workspace that an earlier small call left for a stream is enlarged
+    for the row-block kernel: the same kernel, hence the same bits on inputs
+    whose sums round, as with a workspace of the full size."""
+    fq = gpu_lib
+    M, K, N = 64, 7296, 8192
+    stream = torch.cuda.Stream()
+    p = make_problem(M, K, N, frac=0.01, seed=5)
+    X, Wq, s, z = fq.to_device(p)
+    tc = fq.TileCOODevice(fq.fq_pack_tile_coo(K, N, p.k, p.n, p.v))
+    ws = torch.zeros(fq.fq_workspace_bytes(M, K, N), dtype=torch.uint8, device="cuda")
+    full = fq.fq_w4a16_outlier_matmul(X, Wq, s, z, tc, y_dtype="f32", ws=ws)
+    torch.cuda.synchronize()
+    kept = torch.zeros(256 * 1024, dtype=torch.uint8, device="cuda")   # as a small call leaves it
+    key = (X.device.index, int(stream.cuda_stream))
+    before = fq._workspaces.get(key)   # streams come from a pool: put back what was there
+    fq._workspaces[key] = kept
+    try:
+        torch.cuda.synchronize()
+        y = fq.fq_w4a16_outlier_matmul(X, Wq, s, z, tc, y_dtype="f32", stream=stream)
+        torch.cuda.synchronize()
+        assert fq._workspaces[key].numel() >= fq.fq_workspace_bytes(M, K, N)
+        assert torch.equal(y, full)
+    finally:
+        if before is None:
+            del fq._workspaces[key]
+        else:
+            fq._workspaces[key] = before
