@@ -53,34 +53,35 @@ GEMM_CANDIDATES = 16
 GEMM_WORKSPACE = 64 << 20
 
 
-def rows_kernel_runs(M, K, N):
-    """Whether the row-block kernel takes the call (its planner's rule, for
-    matrices without very full tiles): more than 16 rows and at least 14 tiles
-    of K per workgroup of 128 columns x 64 (32) rows; no split up to 32 rows;
-    rounds of workgroups filled."""
+def rows_kernel_split(M, K, N):
+    """K ranges per column block where the row-block kernel takes the call (its
+    planner's rule, for matrices without very full tiles), else 0: more than 16
+    rows and at least 14 tiles of K per workgroup of 128 columns x 64 (32) rows;
+    no split up to 32 rows; rounds of workgroups filled."""
     if M <= 16:
-        return False
+        return 0
     rows = 32 if M <= 32 else 64
     units = -(-N // 128) * -(-M // rows)
     split = max(1, 256 // units)
     if rows == 32 and split > 1:
-        return False
+        return 0
     split = max(split, -(-(K // 128) // 126))
     rounds = -(-units * split // 256)
     if rounds > 1 and rows == 32:
-        return False
+        return 0
     if rounds > 1 and units * split / (256 * rounds) * M / (rows * -(-M // rows)) < 0.65:
-        return False
-    return K // 128 // split >= 14
+        return 0
+    return split if K // 128 // split >= 14 else 0
 
 
-def kernel_name(fq, M, K, N, packing=None, flags=0):
+def kernel_name(fq, M, K, N, packing=None, flags=0, sizes=None):
     """Template instance of the fused kernel the library launches for (M, K, N),
     a Tile-COO packed with `packing` (default: the library default) and the
-    switches `flags`."""
+    switches `flags`; `sizes`: the Tile-COO's, where its tiles may be full."""
     packing = packing or {}
-    if not flags and rows_kernel_runs(M, K, N):
-        return f"rows_kernel<{1 if M <= 32 else 2}, true, 1>"
+    gl = 2 if sizes and sizes.max_tile_groups > 64 and sizes.n_groups >= 32 * sizes.n_tiles else 1
+    if not flags and rows_kernel_split(M, K, N):
+        return f"rows_kernel<{1 if M <= 32 else 2}, true, {gl}>"
     c = fq.fq_launch_config(M, K, N, buckets_per_tile=packing.get("buckets_per_tile"),
                             group_mode=packing.get("group_mode"), flags=flags)
     mb = 1 if min(M, 32) <= 16 else 2
@@ -90,7 +91,7 @@ def kernel_name(fq, M, K, N, packing=None, flags=0):
     bk = "true" if c["bulk_scales"] else "false"
     dv = "true" if flags & fq.FQ_DENSE_VALU else "false"
     return (f"matmul_kernel<{mb}, {mode}, {c['strip_cols'] // 16}, true, true, "
-            f"{c['dense_waves']}, {sk}, {c['outlier_waves']}, {xs}, {bk}, {dv}, 1>")
+            f"{c['dense_waves']}, {sk}, {c['outlier_waves']}, {xs}, {bk}, {dv}, {gl}>")
 
 
 def dominant_kernel(fq, cases):
@@ -615,7 +616,17 @@ def unfused_workspace_bytes(fq, M, K, N):
 def mfma_flops(fq, M, K, N):
     """FLOPs the matrix cores execute in one fused launch: per 16-row block and
     128 x (strip width) tile, 4 x NCB dense MFMAs, 4 row-sum MFMAs and, with
-    the MFMA outlier mapping, 4 x NCB image MFMAs of 16 x 16 x 32."""
+    the MFMA outlier mapping, 4 x NCB image MFMAs of 16 x 16 x 32.  In the
+    row-block kernel, per 32 columns and tile, 8 dense and 8 image MFMAs of
+    32 x 32 x 16 for each 32-row block and 4 row-sum MFMAs; its two K groups
+    walk equally many tiles, the shorter one its last tile twice."""
+    split = rows_kernel_split(M, K, N)
+    if split:
+        rb = 1 if M <= 32 else 2
+        T = K // 128
+        tiles = sum(2 * -(-((i + 1) * T // split - i * T // split) // 2) for i in range(split))
+        waves = 4 * -(-N // 128) * -(-M // (32 * rb))
+        return waves * tiles * (16 * rb * 32 * 32 * 16 + 4 * 16 * 16 * 32) * 2
     c = fq.fq_launch_config(M, K, N)
     ncb = c["strip_cols"] // 16
     slabs = (M + 31) // 32
@@ -660,7 +671,7 @@ def pmc_summary_mfma(csv_path, log_path):
         raise SystemExit(f"no pmc_large_m line in {log_path}")
     rows = {}
     for r in csv.DictReader(open(csv_path)):
-        if "matmul_kernel" not in r["Kernel_Name"]:
+        if "matmul_kernel" not in r["Kernel_Name"] and "rows_kernel" not in r["Kernel_Name"]:
             continue
         d = rows.setdefault(int(r["Dispatch_Id"]), {})
         d[r["Counter_Name"]] = d.get(r["Counter_Name"], 0.0) + float(r["Counter_Value"])
@@ -960,7 +971,7 @@ def sweep(fq, torch, which, dev, copies_min=4):
             nnz = int(host.sizes.nnz)
             rec = {"sweep": which, "K": K, "N": N, "M": M2, "frac": frac, "dist": dist,
                    "nnz": nnz, "tilecoo_bytes": int(host.sizes.bytes), "bytes": nbytes,
-                   "kernel": kernel_name(fq, M2, K, N), "copies": len(W),
+                   "kernel": kernel_name(fq, M2, K, N, sizes=host.sizes), "copies": len(W),
                    "fused_us": round(us, 3), "fused_GBs": round(nbytes / us / 1e3, 1),
                    "pct_hbm_peak": round(100 * nbytes / us / 1e3 / HBM_PEAK_GBS, 1),
                    "unfused_us": round(us_unf, 3), "dense_only_us": round(us_dense, 3),
