@@ -6,12 +6,14 @@ the 32-, 64- and 128-column blocks among them) and, on every column, the strip
 kernel's, which a forced strip width selects.
 """
 
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
 
 import oracle
-from synth import make_exact_problem, make_problem
+from synth import bf16_bits_from_f32, make_exact_problem, make_problem
 
 pytestmark = pytest.mark.gpu
 
@@ -52,6 +54,30 @@ def test_rows_kernel_bit_exact(gpu_lib, M, K, N, frac, packing):
     assert torch.equal(bf, y.to(torch.bfloat16))
     cols = np.unique(np.concatenate([[0, 1, 31, 32, 63, 64, 127, 128, N - 65, N - 64, N - 33, N - 32, N - 1],
                                      np.random.default_rng(M).choice(N, 32, replace=False)]) % N)
+    exact = oracle.matmul(p.X, p.Wq, p.scales, p.zeros, K, N, p.group, p.k, p.n, p.v, cols)
+    assert np.array_equal(y.cpu().numpy()[:, cols], exact.astype(np.float32))
+
+
+@pytest.mark.parametrize("groups", [64, 65, 129, 160, 161])
+def test_rows_kernel_one_full_tile(gpu_lib, groups):
+    """Sparse tiles and one of `groups` groups: what one group load leaves is
+    loaded inside the tile, and past 160 groups the strip kernel runs."""
+    fq = gpu_lib
+    M, K, N = 50, 1792, 16448
+    p = make_exact_problem(M, K, N, frac=0.0, seed=groups)
+    rng = np.random.Generator(np.random.PCG64(groups))
+    pos = rng.choice(128 * 64, size=4 * groups - 1, replace=False)
+    k = np.concatenate([3 * 128 + pos // 64, rng.choice(128, 9, replace=False) + 4 * 128]).astype(np.int32)
+    n = np.concatenate([5 * 64 + pos % 64, np.full(9, 5 * 64 + 33)]).astype(np.int32)
+    v = rng.integers(1, 33, size=k.size) / 8.0
+    p = dataclasses.replace(p, k=k, n=n, v=bf16_bits_from_f32(v.astype(np.float32)))
+    host = fq.fq_pack_tile_coo(K, N, p.k, p.n, p.v)
+    assert host.sizes.max_tile_groups == groups
+    X, Wq, s, z = fq.to_device(p)
+    print(f"rows kernel, one tile of {groups} groups", flush=True)
+    y = fq.fq_w4a16_outlier_matmul(X, Wq, s, z, fq.TileCOODevice(host), y_dtype="f32")
+    torch.cuda.synchronize()
+    cols = np.concatenate([np.arange(5 * 64 - 2, 6 * 64 + 2), [0, N - 1]])
     exact = oracle.matmul(p.X, p.Wq, p.scales, p.zeros, K, N, p.group, p.k, p.n, p.v, cols)
     assert np.array_equal(y.cpu().numpy()[:, cols], exact.astype(np.float32))
 
