@@ -307,12 +307,36 @@ enum { FQ_DENSE_VALU = 128 };
 fq_status fq_workspace_bytes(const fq_problem* pr, size_t* bytes);
 
 /*
+ * fq_launch_kernel -- the kernel and grid that a matmul call with this problem,
+ * Tile-COO and workspace size launches (for tools, tests and benchmarks;
+ * nothing is launched and no device is needed).  tc as for the fused entry
+ * point, of which only params, n_groups and max_tile_groups are read; NULL: the
+ * dense-only entry point.  workspace_bytes: the workspace's size (SIZE_MAX: any
+ * size that is needed; FQ_NOALLOC_SCRATCH_BYTES: the allocation-free entry
+ * point, where it does not return FQ_ERR_SCRATCH_LIMIT).  Outputs (host):
+ *   out[0] FQ_KERNEL_STRIP (fq_launch_config gives its further switches) or
+ *          FQ_KERNEL_ROWS, the row-block kernel for more than 16 rows, whose
+ *          workgroups share X, its row sums and each other's turn on the matrix
+ *          cores: eight waves, two halves of its K range times four column waves
+ *   out[1] columns and out[2] rows of a workgroup's block of Y, out[3] blocks
+ *          along the rows of Y
+ *   out[4] K ranges per block (split)   out[5] workgroups in the grid
+ *   out[6] waves per workgroup          out[7] loads of 64 outlier groups per
+ *          tile: 1, 2 where tiles are full, 0 without outliers
+ *   out[8] dynamic LDS bytes per workgroup
+ *   out[9] bytes of split-K partial sums, in KiB
+ * Errors: FQ_ERR_NULL, FQ_ERR_SHAPE, FQ_ERR_FORMAT, FQ_ERR_UNSUPPORTED,
+ * FQ_ERR_WORKSPACE (workspace_bytes too small for any launch).
+ */
+enum { FQ_KERNEL_STRIP = 0, FQ_KERNEL_ROWS = 1 };
+fq_status fq_launch_kernel(const fq_problem* pr, const fq_tilecoo_dev* tc, size_t workspace_bytes,
+                           int32_t out[10]);
+
+/*
  * fq_launch_config -- the strip kernel's launch for pr and a Tile-COO with the
  * given buckets_per_tile (1..256) and group_mode (for tools and benchmarks;
- * nothing is launched).  It is the launch the fused entry point makes with at
- * most 16 rows, with a forced split or a schedule or strip switch, and where
- * workgroups would get few tiles; with more rows and a long K, the row-block
- * kernel runs instead, whose grid these fields do not describe.  Outputs (host):
+ * nothing is launched).  With more than 16 rows it is the launch that the fused
+ * entry point makes only where fq_launch_kernel names that kernel.  Outputs (host):
  *   cfg[0] strip width in columns (32 or 64)   cfg[1] K ranges per strip (split)
  *   cfg[2] dense waves per workgroup           cfg[3] outlier-only waves per workgroup
  *   cfg[4] outlier mapping (FQ_SPARSE_GATHER or FQ_SPARSE_MFMA)

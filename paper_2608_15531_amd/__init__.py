@@ -110,6 +110,8 @@ _SIGS = {
     "fq_debug_decode_tile_coo": ([C.POINTER(fq_tilecoo_dev), C.c_int32, C.c_int32, _P, _P, _P,
                                   _P], C.c_int),
     "fq_status_string": ([C.c_int], C.c_char_p),
+    "fq_launch_kernel": ([C.POINTER(fq_problem), C.POINTER(fq_tilecoo_dev), C.c_size_t,
+                          C.POINTER(C.c_int32)], C.c_int),
     "fq_launch_config": ([C.POINTER(fq_problem), C.c_int32, C.c_int32, C.POINTER(C.c_int32)],
                          C.c_int),
     "fq_quantize_outlier_aware": ([C.c_int32, C.c_int32, _P, C.c_int32, C.c_double,
@@ -525,10 +527,30 @@ def fq_debug_decode_tile_coo(tc: TileCOODevice, K: int, N: int, stream=None):
     return k[:4 * G], n[:4 * G], v[:4 * G]
 
 
+def fq_launch_kernel(M: int, K: int, N: int, tc=None, split_k: int = 0, sparse: str = "auto",
+                     flags: int = 0, workspace_bytes: int | None = None) -> dict:
+    """The kernel and grid of a matmul call (nothing is launched).  tc: a TileCOOHost
+    or TileCOODevice, or None for the dense-only entry point.  workspace_bytes: the
+    workspace's size (default: any size that is needed)."""
+    lib = load()
+    pr = _problem(M, K, N, FQ_Y_BF16, split_k, 128, sparse, flags)
+    dev = None
+    if tc is not None:
+        dev = C.byref(fq_tilecoo_dev(None, None, None, tc.params, tc.sizes.n_groups,
+                                     tc.sizes.max_tile_groups))
+    if workspace_bytes is None:
+        workspace_bytes = C.c_size_t(-1).value
+    out = (C.c_int32 * 10)()
+    _check(lib.fq_launch_kernel(C.byref(pr), dev, workspace_bytes, out), "fq_launch_kernel")
+    return {"kernel": "rows" if out[0] else "strip", "block_cols": out[1], "block_rows": out[2],
+            "row_blocks": out[3], "split_k": out[4], "workgroups": out[5], "waves": out[6],
+            "group_loads": out[7], "lds_bytes": out[8], "partial_kib": out[9]}
+
+
 def fq_launch_config(M: int, K: int, N: int, split_k: int = 0, sparse: str = "auto",
                      flags: int = 0, buckets_per_tile: int | None = None,
                      group_mode: int | None = None) -> dict:
-    """The strip kernel's launch (nothing is launched; see fq.h for when it runs) for a
+    """The strip kernel's launch (nothing is launched; fq_launch_kernel says when it runs) for a
     Tile-COO packed with the given bucket count and grouping (default: the
     library's default packing)."""
     lib = load()

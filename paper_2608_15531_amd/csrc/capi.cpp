@@ -43,18 +43,24 @@ fq_status check_dense_ptrs(const uint16_t* X, const uint32_t* Wq, const uint16_t
   return FQ_OK;
 }
 
-fq_status check_tc(const fq_problem* pr, const fq_tilecoo_dev* tc) {
-  if (!tc) return FQ_ERR_NULL;
+// The checks of a Tile-COO that need none of its arrays.
+fq_status check_tc_sizes(const fq_tilecoo_dev* tc) {
   const fq_tilecoo_params& p = tc->params;
   if (p.k_tile != fqi::kTileK || p.n_tile != fqi::kTileN) return FQ_ERR_UNSUPPORTED;
   if (p.buckets_per_tile < 1 || p.buckets_per_tile > fqi::kMaxBuckets) return FQ_ERR_UNSUPPORTED;
   if (p.group_mode != FQ_GROUP_BY_COLUMN && p.group_mode != FQ_GROUP_BY_BUCKET) return FQ_ERR_FORMAT;
   if (tc->n_groups < 0 || tc->max_tile_groups < 0) return FQ_ERR_FORMAT;
   if (tc->n_groups >= (int64_t(1) << 27)) return FQ_ERR_UNSUPPORTED;   // 16-byte groups < 2^31 B
+  return FQ_OK;
+}
+
+fq_status check_tc(const fq_tilecoo_dev* tc) {
+  if (!tc) return FQ_ERR_NULL;
+  const fq_status st = check_tc_sizes(tc);
+  if (st != FQ_OK) return st;
   if (!tc->tile_indptr || !tc->bucket_info || (tc->n_groups > 0 && !tc->packed)) return FQ_ERR_NULL;
   if (!aligned(tc->tile_indptr, 4) || !aligned(tc->bucket_info, 4) || !aligned(tc->packed, 16))
     return FQ_ERR_ALIGN;
-  (void)pr;
   return FQ_OK;
 }
 
@@ -80,6 +86,16 @@ bool plan_for(const fq_problem* pr, const fq_tilecoo_dev* tc, bool dense, bool s
                         sparse ? tc->max_tile_groups : 0, plan, mode, plan_opts(pr));
 }
 
+// Whether the launch of `plan` fits a workspace of this size; one that holds
+// the strip kernel's partial sums only gets that kernel.
+bool fit_workspace(fqi::Plan* plan, size_t workspace_bytes) {
+  if (workspace_bytes < plan->ws_bytes && workspace_bytes >= plan->strip_ws_bytes) {
+    plan->rows_RB = 0;
+    plan->ws_bytes = plan->strip_ws_bytes;
+  }
+  return workspace_bytes >= plan->ws_bytes;
+}
+
 fq_status run(const fq_problem* pr, const uint16_t* X, const uint32_t* Wq,
               const uint16_t* scales, const uint32_t* zeros, const fq_tilecoo_dev* tc, void* Y,
               void* workspace, size_t workspace_bytes, void* stream, bool dense, bool sparse,
@@ -87,12 +103,7 @@ fq_status run(const fq_problem* pr, const uint16_t* X, const uint32_t* Wq,
   fqi::Plan plan;
   if (!plan_for(pr, tc, dense, sparse, &plan)) return FQ_ERR_UNSUPPORTED;
   if (!workspace) return FQ_ERR_WORKSPACE;
-  // a workspace that holds the strip kernel's partial sums only: that kernel
-  if (workspace_bytes < plan.ws_bytes && workspace_bytes >= plan.strip_ws_bytes) {
-    plan.rows_RB = 0;
-    plan.ws_bytes = plan.strip_ws_bytes;
-  }
-  if (workspace_bytes < plan.ws_bytes || !aligned(workspace, 256)) return FQ_ERR_WORKSPACE;
+  if (!fit_workspace(&plan, workspace_bytes) || !aligned(workspace, 256)) return FQ_ERR_WORKSPACE;
   fqi::MatmulPtrs p{};
   p.X = X;
   p.Wq = Wq;
@@ -168,6 +179,29 @@ fq_status fq_launch_config(const fq_problem* pr, int32_t buckets_per_tile, int32
   return FQ_OK;
 }
 
+fq_status fq_launch_kernel(const fq_problem* pr, const fq_tilecoo_dev* tc, size_t workspace_bytes,
+                           int32_t out[10]) {
+  if (!out) return FQ_ERR_NULL;
+  fq_status st = check_problem(pr);
+  if (st == FQ_OK && tc) st = check_tc_sizes(tc);
+  if (st != FQ_OK) return st;
+  fqi::Plan pl;
+  if (!plan_for(pr, tc, true, tc != nullptr, &pl)) return FQ_ERR_UNSUPPORTED;
+  if (!fit_workspace(&pl, workspace_bytes)) return FQ_ERR_WORKSPACE;
+  const bool rows = pl.rows_RB != 0;
+  out[0] = rows ? FQ_KERNEL_ROWS : FQ_KERNEL_STRIP;
+  out[1] = rows ? 128 : 16 * pl.NCB;
+  out[2] = rows ? 32 * pl.rows_RB : pl.slab_M;
+  out[3] = rows ? pl.rows_blocks : pl.n_slabs;
+  out[4] = rows ? pl.rows_S : pl.S;
+  out[5] = rows ? pl.rows_G * pl.rows_blocks : pl.G * pl.n_slabs;
+  out[6] = rows ? 8 : pl.NW + pl.NWS;
+  out[7] = fqi::group_loads(pl, tc ? tc->n_groups : 0, tc != nullptr);
+  out[8] = int32_t(rows ? fqi::rows_lds_bytes(pl) : pl.lds_bytes);
+  out[9] = int32_t((rows ? pl.rows_partial_bytes : pl.partial_bytes) >> 10);
+  return FQ_OK;
+}
+
 fq_status fq_workspace_bytes(const fq_problem* pr, size_t* bytes) {
   if (!bytes) return FQ_ERR_NULL;
   fq_status st = check_problem(pr);
@@ -205,7 +239,7 @@ fq_status fq_w4a16_outlier_matmul(const fq_problem* pr, const uint16_t* X, const
                                   size_t workspace_bytes, void* stream) {
   fq_status st = check_problem(pr);
   if (st == FQ_OK) st = check_dense_ptrs(X, Wq, scales, zeros, Y);
-  if (st == FQ_OK) st = check_tc(pr, tc);
+  if (st == FQ_OK) st = check_tc(tc);
   if (st != FQ_OK) return st;
   return run(pr, X, Wq, scales, zeros, tc, Y, workspace, workspace_bytes, stream, true, true,
              nullptr);
@@ -217,7 +251,7 @@ fq_status fq_w4a16_outlier_matmul_noalloc(const fq_problem* pr, const uint16_t* 
                                           void* Y, void* stream) {
   fq_status st = check_problem(pr);
   if (st == FQ_OK) st = check_dense_ptrs(X, Wq, scales, zeros, Y);
-  if (st == FQ_OK) st = check_tc(pr, tc);
+  if (st == FQ_OK) st = check_tc(tc);
   if (st != FQ_OK) return st;
   // the same plan the workspace entry point makes; its workspace must fit
   // the static scratch (checked before the device is touched)
@@ -247,7 +281,7 @@ fq_status fq_w4a16_outlier_matmul_unfused(const fq_problem* pr, const uint16_t* 
                                           void* stream) {
   fq_status st = check_problem(pr);
   if (st == FQ_OK) st = check_dense_ptrs(X, Wq, scales, zeros, Y);
-  if (st == FQ_OK) st = check_tc(pr, tc);
+  if (st == FQ_OK) st = check_tc(tc);
   if (st != FQ_OK) return st;
   size_t need = 0, base = 0;
   if ((st = fq_workspace_bytes_unfused(pr, &need)) != FQ_OK) return st;

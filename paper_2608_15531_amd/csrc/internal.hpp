@@ -68,6 +68,7 @@ struct Plan {
   // 32-row blocks per workgroup (0: the strip kernel runs), row blocks of M,
   // K ranges and workgroups per row block
   int rows_RB, rows_blocks, rows_S, rows_G;
+  size_t rows_partial_bytes;
 };
 
 // Schedule options of make_plan (bit set).
@@ -98,11 +99,17 @@ struct MatmulPtrs {
   void* workspace;
 };
 
+// Loads of 64 outlier groups a tile issues (kernels.hip): 1, or 2 where the
+// tiles are full; 0 without outliers.  Only the MFMA mapping under uniform
+// split-K without outlier waves, and the row-block kernel, have the second.
+int group_loads(const Plan& plan, int64_t n_groups, bool sparse);
+
 // Adds the row-block kernel's launch to a plan made without a forced split or
 // schedule switch, where that kernel is the faster one (rows.hip).
 void plan_rows(Plan* plan);
 int launch_rows(const Plan& plan, const MatmulPtrs& p, bool sparse, bool two_group_loads,
                 void* stream);
+size_t rows_lds_bytes(const Plan& plan);
 
 // Enqueues one matmul kernel; returns a hipError_t value (0 on success).
 int launch_matmul(const Plan& plan, const MatmulPtrs& p, bool dense, bool sparse, void* stream);

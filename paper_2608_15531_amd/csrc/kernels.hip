@@ -1529,6 +1529,17 @@ bool make_plan(int M, int K, int N, int split_k, bool dense, bool sparse, int B,
   return true;
 }
 
+// A second group load per tile where some tile needs it and the average tile
+// is half way there: 4096 x 14336 at 8 rows, 5 % outliers 17.3 -> 14.8 us (103
+// groups a tile), half of them in 2 % of the columns 23.0 -> 20.1; at 2 %,
+// whose tiles hold at most 54, one load (13.2 us).
+int group_loads(const Plan& pl, int64_t n_groups, bool sparse) {
+  if (!sparse || n_groups == 0) return 0;
+  const int64_t tiles = int64_t(pl.T) * (pl.N / kTileN);
+  const bool built = pl.rows_RB || (pl.MODE == 1 && !pl.stream && pl.NWS == 0 && !pl.DV);
+  return built && pl.max_tile_groups > 64 && n_groups >= 32 * tiles ? 2 : 1;
+}
+
 int launch_matmul(const Plan& pl, const MatmulPtrs& p, bool dense, bool sparse, void* stream) {
   fqk::MatmulArgs a{};
   a.X = p.X;
@@ -1551,12 +1562,7 @@ int launch_matmul(const Plan& pl, const MatmulPtrs& p, bool dense, bool sparse, 
   a.G = pl.G;
   a.C = pl.C;
   a.n_slabs = pl.n_slabs;
-  // A second group load per tile where some tile needs it and the average tile
-  // is half way there: 4096 x 14336 at 8 rows, 5 % outliers 17.3 -> 14.8 us (103
-  // groups a tile), half of them in 2 % of the columns 23.0 -> 20.1; at 2 %,
-  // whose tiles hold at most 54, one load (13.2 us).
-  const int64_t tiles = int64_t(pl.T) * (pl.N / kTileN);
-  a.two_group_loads = pl.max_tile_groups > 64 && p.n_groups >= 32 * tiles;
+  a.two_group_loads = group_loads(pl, p.n_groups, sparse) == 2;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (sparse && p.n_groups == 0) {
     // No outliers: the fused launch drops its sparse half; a sparse-only

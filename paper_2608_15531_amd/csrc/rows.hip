@@ -630,7 +630,12 @@ void plan_rows(Plan* p) {
   p->rows_blocks = blocks;
   p->rows_S = S;
   p->rows_G = n_cb * S;
+  p->rows_partial_bytes = size_t(part);
   p->ws_bytes = std::max(p->ws_bytes, kCounterRegion + size_t(part));
+}
+
+size_t rows_lds_bytes(const Plan& pl) {
+  return pl.rows_RB == 1 ? size_t(fqk::RowsLds<1>::bytes) : size_t(fqk::RowsLds<2>::bytes);
 }
 
 int launch_rows(const Plan& pl, const MatmulPtrs& p, bool sparse, bool two_group_loads, void* stream) {

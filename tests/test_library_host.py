@@ -4,6 +4,7 @@ oracle's independent packer, validation, and the C ABI's argument checks."""
 import ctypes as C
 import os
 import re
+import types
 
 import numpy as np
 import pytest
@@ -610,3 +611,94 @@ def test_launch_plans_stay_within_kernel_limits(lib):
                             share = min(T, -(-U // c["workgroups"]))
                             assert -(-share // c["dense_waves"]) <= 63, where
     assert accepted > 10000
+
+
+def _coo(n_groups, max_tile_groups, group_mode=None):
+    """What fq_launch_kernel reads of a Tile-COO: its parameters and sizes."""
+    p = fq.load().fq_default_tilecoo_params()
+    if group_mode is not None:
+        p.group_mode = group_mode
+    sizes = fq.fq_tilecoo_sizes()
+    sizes.n_groups, sizes.max_tile_groups = n_groups, max_tile_groups
+    return types.SimpleNamespace(params=p, sizes=sizes)
+
+
+def _uniform(K, N, per_tile, fullest=None):
+    return _coo(K // 128 * (N // 64) * per_tile, fullest or per_tile + 10)
+
+
+def test_launch_kernel_names_what_runs(lib):
+    """The kernel, its grid and its group loads: by rows, forced split, switches,
+    mapping, full tiles and workspace size."""
+    K, N, tc = 4096, 28672, _uniform(4096, 28672, 21)
+    rows = fq.fq_launch_kernel(128, K, N, tc)
+    assert (rows["kernel"], rows["block_cols"], rows["block_rows"], rows["row_blocks"]) == ("rows", 128, 64, 2)
+    assert rows["workgroups"] == 448 and rows["waves"] == 8 and rows["group_loads"] == 1
+    assert fq.fq_launch_kernel(27, K, N, tc)["block_rows"] == 32
+    for kw in ({"split_k": 1}, {"flags": fq.FQ_STRIP_64}, {"flags": fq.FQ_FOUR_WAVES},
+               {"flags": fq.FQ_SCHED_STREAM_K}):
+        assert fq.fq_launch_kernel(128, K, N, tc, **kw)["kernel"] == "strip", kw
+    for M in (1, 16):
+        s = fq.fq_launch_kernel(M, K, N, tc)
+        c = fq.fq_launch_config(M, K, N)
+        assert s["kernel"] == "strip" and s["block_cols"] == c["strip_cols"]
+        assert (s["split_k"], s["workgroups"], s["lds_bytes"]) == (c["split_k"], c["workgroups"], c["lds_bytes"])
+    # group loads: two where tiles are full, none without outliers
+    full = _uniform(K, N, 103, 124)
+    assert fq.fq_launch_kernel(128, K, N, full)["group_loads"] == 2
+    assert fq.fq_launch_kernel(8, K, N, full)["group_loads"] == 2
+    assert fq.fq_launch_kernel(8, K, N, full, flags=fq.FQ_SPARSE_WAVES)["group_loads"] == 1
+    assert fq.fq_launch_kernel(8, K, N, full, flags=fq.FQ_SCHED_STREAM_K)["group_loads"] == 1
+    assert fq.fq_launch_kernel(1, K, N, _coo(10 ** 6, 124, fq.FQ_GROUP_BY_COLUMN))["group_loads"] == 1
+    assert fq.fq_launch_kernel(8, K, N, _uniform(K, N, 31, 90))["group_loads"] == 1
+    assert fq.fq_launch_kernel(8, K, N, _coo(0, 0))["group_loads"] == 0
+    assert fq.fq_launch_kernel(8, K, N)["group_loads"] == 0
+    # the fullest tile's limit
+    assert fq.fq_launch_kernel(128, K, N, _uniform(K, N, 60, 160))["kernel"] == "rows"
+    assert fq.fq_launch_kernel(128, K, N, _uniform(K, N, 60, 161))["kernel"] == "strip"
+    # a workspace for the strip kernel's partial sums only gets that kernel
+    K, N, tc = 7296, 8192, _uniform(7296, 8192, 21)
+    need = fq.fq_workspace_bytes(64, K, N)
+    assert fq.fq_launch_kernel(64, K, N, tc, workspace_bytes=need)["kernel"] == "rows"
+    assert fq.fq_launch_kernel(64, K, N, tc, workspace_bytes=need - 1)["kernel"] == "strip"
+    assert fq.fq_launch_kernel(64, K, N, tc, workspace_bytes=256 * 1024)["kernel"] == "strip"
+    for args in ((129, K, N), (64, K + 1, N)):
+        with pytest.raises(fq.FqError):
+            fq.fq_launch_kernel(*args, tc)
+    with pytest.raises(fq.FqError) as e:
+        fq.fq_launch_kernel(64, K, N, tc, workspace_bytes=256 * 1024 - 1)
+    assert e.value.name == "FQ_ERR_WORKSPACE"
+
+
+def test_rows_plans_stay_within_kernel_limits(lib):
+    """Every row-block launch over a sweep of shapes: at most 63 tiles per K group,
+    one counter per block, partial sums that the static scratch and the size
+    fq_workspace_bytes gives hold, LDS of one CU, and a grid that covers Y."""
+    seen = set()
+    for M in (17, 24, 25, 32, 33, 64, 65, 96, 97, 128):
+        for T in (1, 14, 15, 20, 32, 57, 64, 112, 126, 127, 224, 253, 448, 512):
+            for N in (64, 192, 512, 2048, 4096, 6144, 8192, 8256, 14336, 16448, 28672, 32832, 57344, 131136):
+                K = 128 * T
+                if K * N // 2 >= 1 << 31:
+                    continue
+                need = fq.fq_workspace_bytes(M, K, N)
+                for tc in (None, _coo(0, 0), _uniform(K, N, 21), _uniform(K, N, 100, 120)):
+                    if tc is not None and tc.sizes.n_groups >= 1 << 27:
+                        continue
+                    c = fq.fq_launch_kernel(M, K, N, tc, workspace_bytes=need)
+                    if c["kernel"] != "rows":
+                        continue
+                    S, rb = c["split_k"], c["block_rows"] // 32
+                    seen.add((rb, S > 1, c["row_blocks"]))
+                    cols = -(-N // 128)
+                    where = (M, K, N, c)
+                    assert c["block_rows"] == (32 if M <= 32 else 64), where
+                    assert c["row_blocks"] == -(-M // c["block_rows"]), where
+                    assert c["workgroups"] == cols * S * c["row_blocks"], where
+                    assert T // S >= 14 and -(-(-(-T // S)) // 2) <= 63, where
+                    assert cols * c["row_blocks"] <= 65536, where
+                    part = cols * c["row_blocks"] * S * 4 * rb * 4096 if S > 1 else 0
+                    assert c["partial_kib"] * 1024 == part <= 8 << 20, where
+                    assert 256 * 1024 + part <= need, where
+                    assert c["lds_bytes"] <= 160 * 1024, where
+    assert {(1, False, 1), (2, False, 1), (2, True, 1), (2, False, 2), (2, True, 2)} <= seen
