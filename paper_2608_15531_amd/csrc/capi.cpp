@@ -82,7 +82,7 @@ bool plan_for(const fq_problem* pr, const fq_tilecoo_dev* tc, bool dense, bool s
               fqi::Plan* plan) {
   const int mode = plan_mode(pr, sparse ? tc->params.group_mode : FQ_GROUP_BY_COLUMN);
   return fqi::make_plan(pr->M, pr->K, pr->N, pr->split_k, dense, sparse,
-                        sparse ? tc->params.buckets_per_tile : 0,
+                        sparse ? tc->params.buckets_per_tile : 0, sparse ? tc->n_groups : 0,
                         sparse ? tc->max_tile_groups : 0, plan, mode, plan_opts(pr));
 }
 
@@ -163,8 +163,8 @@ fq_status fq_launch_config(const fq_problem* pr, int32_t buckets_per_tile, int32
   if (group_mode != FQ_GROUP_BY_COLUMN && group_mode != FQ_GROUP_BY_BUCKET) return FQ_ERR_FORMAT;
   const int mode = plan_mode(pr, group_mode);
   fqi::Plan pl;
-  if (!fqi::make_plan(pr->M, pr->K, pr->N, pr->split_k, true, true, buckets_per_tile, 0, &pl, mode,
-                      plan_opts(pr)))
+  if (!fqi::make_plan(pr->M, pr->K, pr->N, pr->split_k, true, true, buckets_per_tile, 0, 0, &pl,
+                      mode, plan_opts(pr)))
     return FQ_ERR_UNSUPPORTED;
   cfg[0] = 16 * pl.NCB;
   cfg[1] = pl.S;
@@ -207,14 +207,15 @@ fq_status fq_workspace_bytes(const fq_problem* pr, size_t* bytes) {
   fq_status st = check_problem(pr);
   if (st != FQ_OK) return st;
   // The split, and with it the partial-sum area, depends on the kernel the
-  // call launches: size for the largest of dense-only and both mappings.
+  // call launches: size for the largest of dense-only, both mappings and a
+  // Tile-COO without groups.
   fqi::Plan pl;
   size_t need = 0;
   bool any = false;
   for (int mode = -1; mode <= 1; ++mode) {
-    for (int sparse = 0; sparse <= 1; ++sparse) {
-      if (fqi::make_plan(pr->M, pr->K, pr->N, pr->split_k, true, sparse != 0, 1, 0, &pl, mode,
-                         plan_opts(pr))) {
+    for (int sparse = 0; sparse <= 2; ++sparse) {   // 2: with groups
+      if (fqi::make_plan(pr->M, pr->K, pr->N, pr->split_k, true, sparse != 0, 1, sparse / 2, 0, &pl,
+                         mode, plan_opts(pr))) {
         any = true;
         need = pl.ws_bytes > need ? pl.ws_bytes : need;
       }

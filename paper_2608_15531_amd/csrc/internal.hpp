@@ -81,7 +81,8 @@ constexpr int kOptDenseValu = 32;     // dense products by VALU dot products (M 
 
 // Returns false when (M, K, N) is outside what the kernels implement.
 // mode: -1 picks the sparse mapping by M, 0 forces gathers, 1 forces MFMA.
-bool make_plan(int M, int K, int N, int split_k, bool dense, bool sparse, int B,
+// n_groups: the Tile-COO's groups (a fused call with none runs dense only).
+bool make_plan(int M, int K, int N, int split_k, bool dense, bool sparse, int B, int64_t n_groups,
                int64_t max_tile_groups, Plan* plan, int mode = -1, int opts = 0);
 
 struct MatmulPtrs {
@@ -106,7 +107,7 @@ int group_loads(const Plan& plan, int64_t n_groups, bool sparse);
 
 // Adds the row-block kernel's launch to a plan made without a forced split or
 // schedule switch, where that kernel is the faster one (rows.hip).
-void plan_rows(Plan* plan);
+void plan_rows(Plan* plan, bool outliers);
 int launch_rows(const Plan& plan, const MatmulPtrs& p, bool sparse, bool two_group_loads,
                 void* stream);
 size_t rows_lds_bytes(const Plan& plan);

@@ -1381,7 +1381,7 @@ Shape default_shape(int T, int N, int n_slabs, int slab_M) {
 }
 }  // namespace
 
-bool make_plan(int M, int K, int N, int split_k, bool dense, bool sparse, int B,
+bool make_plan(int M, int K, int N, int split_k, bool dense, bool sparse, int B, int64_t n_groups,
                int64_t max_tile_groups, Plan* pl, int mode, int opts) {
   if (M < 1 || M > kMaxM || K < kTileK || N < kTileN || K % kTileK || N % kTileN) return false;
   if (N / kTileN > kMaxStrips) return false;
@@ -1524,7 +1524,7 @@ bool make_plan(int M, int K, int N, int split_k, bool dense, bool sparse, int B,
   const size_t lim = size_t(1) << 31;
   if (size_t(K) * N / 2 >= lim || size_t(M) * K * 2 >= lim || p.partial_bytes >= lim) return false;
   p.ws_bytes = p.strip_ws_bytes = kCounterRegion + align_up(p.partial_bytes, 256);
-  if (dense && split_k == 0 && opts == 0 && mode != 0) plan_rows(&p);
+  if (dense && split_k == 0 && opts == 0 && mode != 0) plan_rows(&p, sparse && n_groups > 0);
   *pl = p;
   return true;
 }

@@ -584,16 +584,69 @@ int launch_rows_variant(const fqi::Plan& pl, const fqi::MatmulPtrs& p, hipStream
 
 namespace fqi {
 
+// Whether the row-block kernel is faster than the strip kernel's plan `p`, for rb
+// 32-row blocks per workgroup, S K ranges, units blocks of Y and so many rounds of
+// workgroups.  Figures: strip kernel's time over the row-block kernel's (above 1 the
+// latter is faster), graph replay, rotated weights, at K x N and the rows given.
+//
+// Measure: `strips` workgroups of the strip kernel on the busiest CU (two run at a
+// time), each with tiles of up to 32 rows x 64 columns, against this kernel's rounds;
+// x = theirs / ours, the strip tiles of a CU per tile of this kernel, of which four
+// cover a tile of 64 rows x 128 columns.
+//
+// 64-row blocks with outliers (a tile takes 0.775 us, a strip tile 0.29): from x = 3
+// on, with a split, whose partial sums cost about 3 us, from 3.5.  At x = 2 -- 65 to
+// 96 rows and 8192 < N <= 10880, half of the CUs and at most 3/4 of the rows used --
+// 4096 x 8576 0.82 to 0.84, 14336 x 8576 0.74 to 0.76, 4096 x 10880 0.85; at x = 3
+// 4096 x 11008 at 65 rows 1.10, split 17280 x 4352 0.95.  More than eight K ranges
+// also need x = 5 or two strip workgroups on a CU (28672 x 2048, 16 ranges, x = 4: 0.92
+// to 0.96; 28672 x 1024 at 65 to 96 rows, two per CU, 1.14 to 1.19).
+//
+// 64-row blocks without outliers (0.635 against 0.19 us): from x = 3.5 on (4096 x
+// 28672 at 112 rows 1.04, at 33 1.16); from 3.3 up to 20 tiles (2560 x 38400 1.05;
+// 4096 x 38400 0.97); from 3 in a single round up to 24 tiles, 18 where the last block
+// has at most 16 rows (2688 x 22336 at 33 rows 1.07, 4096 x 16512 0.93; 2560 x 11008 at
+// 65 rows 0.96).  With a split from x = 5 on; at x = 4 where the strip kernel splits
+// too on two workgroups per CU (14336 x 2048 at 65 to 96 rows 1.14 to 1.20), with a
+// nearly full last block from 20 tiles on (5120 x 13824 at 64 rows 1.11), and from 28
+// where two strip workgroups share a CU (8192 x 11008 at 33 rows 1.05; 4096 x 11008, 16
+// tiles, 0.95; 14336 x 4096 at 65 rows, one per CU, 0.91).
+//
+// 32-row blocks do the work of the two strip workgroups that they replace and save
+// one start: 25 to 32 rows up to 80 tiles (8192 x 28672 at 28 rows 1.04, 12288 x 16512
+// 0.99); up to 24 rows, where strip tiles stage less X, up to 40 tiles, 24 where fewer
+// than 140 CUs get a block (4096 x 18432 to 24576 1.02 to 1.05, 4096 x 16512 0.98 to
+// 1.00, 8192 x 16512 0.96).  Without outliers up to 64 tiles from 21 rows on (8192 x
+// 20480 at 24 rows 1.10), below up to 24 (4096 x 28672 at 17 rows 0.93).
+static bool rows_faster(const Plan& p, int rb, int blocks, int S, int64_t units, int64_t rounds,
+                        bool outliers) {
+  if (rb == 1)
+    return p.T <= (p.M > 24 ? 80 : units < 140 ? 24 : outliers ? 40 : p.M > 20 ? 64 : 24);
+  const int64_t strips = (int64_t(p.G) * p.n_slabs + 255) / 256;
+  const int64_t theirs = strips * S, ours = rounds * p.S;
+  if (outliers) {
+    if (S == 1) return theirs >= 3 * ours;
+    return 2 * theirs >= 7 * ours && (S <= 8 || theirs >= 5 * ours || strips >= 2);
+  }
+  const int tiles = p.T / S, last = p.M - 64 * (blocks - 1);   // rows of the last block
+  if (S == 1)
+    return 2 * theirs >= 7 * ours || (3 * theirs >= 10 * ours && tiles <= 20) ||
+           (rounds == 1 && theirs >= 3 * ours && tiles <= (last > 16 ? 24 : 18));
+  if (theirs >= 5 * ours) return true;
+  if (theirs < 4 * ours) return false;
+  return (strips >= 2 && (p.S > 1 || tiles >= 28)) || (last > 48 && tiles >= 20);
+}
+
 // The row-block kernel's launch for a problem the strip kernel's plan accepts:
 // blocks of 64 rows, 32 up to 32 rows.  The split fills the CUs with one
 // workgroup each.
-// It takes more than 32 rows where every workgroup then has at least
-// kRowsMinTiles tiles: below, its start (two tiles of loads, an LDS exchange)
+// It takes the calls that rows_faster gives it, where every workgroup has at
+// least kRowsMinTiles tiles: below, its start (two tiles of loads, an LDS exchange)
 // and the partial sums of the larger blocks cost more than the shared work
 // saves (64 rows: 14336 x 4096, 14 tiles, 26.0 against 27.6 us; 4096 x 6144, 6
 // tiles, 17.4 against 16.7; 4096 x 4096, 4 tiles, 16.9 against 13.9.  128 rows:
 // 4096 x 4096, 8 tiles, 17.8 against 16.8; 4096 x 6144, 16 tiles, 22.8 against
-// 26.0).  17 to 32 rows only without a split (27 rows: 4096 x 28672 27.0 against
+// 26.0).  Up to 32 rows only without a split (27 rows: 4096 x 28672 27.0 against
 // 28.8 us, 4096 x 14336 split 2 18.6 against 18.5).
 // A matrix with a tile of more than kRowsMaxGroups groups is left to the strip
 // kernel, whose waves do not wait for one another at every tile (5 % outliers,
@@ -603,12 +656,11 @@ namespace fqi {
 // More than one round of workgroups has to be filled, in CUs and rows together, by
 // kRowsMinFill (4096 x 38400 at 64 rows, 300 workgroups, 0.59: 68.9 against 62.6 us;
 // 4096 x 28672 at 80 rows, 0.55: 67.6 against 67.7, at 128 rows, 0.88: 68.1 against
-// 79.8).  A single round that leaves CUs idle still gains (4096 x 16512 at 64 rows,
-// 129 workgroups, 33.2 against 37.9); with 17 to 32 rows only a single round does
-// (8192 x 57344 at 32 rows 98.4 against 97.2).
+// 79.8); up to 32 rows only a single round gains (8192 x 57344 at 32 rows 98.4
+// against 97.2).
 // Partial sums beyond kRowsPartialLimit are left to the strip kernel, so that
 // every default launch fits the static scratch.
-void plan_rows(Plan* p) {
+void plan_rows(Plan* p, bool outliers) {
   p->rows_RB = 0;
   if (p->M <= kRowsMinM || p->max_tile_groups > kRowsMaxGroups) return;
   const int rb = p->M <= 32 ? 1 : 2;
@@ -623,6 +675,7 @@ void plan_rows(Plan* p) {
   const int64_t wgs = units * S, rounds = (wgs + 255) / 256;
   if (rounds > 1 && rb == 1) return;
   if (rounds > 1 && double(wgs) / double(256 * rounds) * p->M / (32 * rb * blocks) < kRowsMinFill) return;
+  if (!rows_faster(*p, rb, blocks, S, units, rounds, outliers)) return;
   const int64_t part = S > 1 ? units * S * fqk::kCW * rb * 4 * 1024 : 0;
   if (part > int64_t(kRowsPartialLimit)) return;
   if (int64_t(n_cb) * S >= (1 << fqk::kRowsGBits) || units > kMaxStrips) return;

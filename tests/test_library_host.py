@@ -702,3 +702,33 @@ def test_rows_plans_stay_within_kernel_limits(lib):
                     assert 256 * 1024 + part <= need, where
                     assert c["lds_bytes"] <= 160 * 1024, where
     assert {(1, False, 1), (2, False, 1), (2, True, 1), (2, False, 2), (2, True, 2)} <= seen
+
+
+# (M, K, N, outliers, kernel): the faster of the two by at least 2 % where both
+# were timed, on either side of each line that the planner draws
+FASTER = [
+    (65, 3840, 8576, True, "strip"), (96, 14336, 8576, True, "strip"), (80, 4096, 10880, True, "strip"),
+    (65, 4096, 11008, True, "rows"), (97, 4096, 8576, True, "rows"), (64, 8192, 8576, True, "rows"),
+    (64, 4096, 38400, True, "strip"), (33, 1792, 16512, True, "rows"), (128, 4096, 6144, True, "rows"),
+    (65, 4096, 8576, False, "strip"), (33, 4096, 16512, False, "strip"), (48, 1792, 20480, False, "rows"),
+    (65, 4096, 14336, False, "strip"), (112, 4096, 28672, False, "rows"), (33, 4096, 28672, False, "rows"),
+    (65, 4096, 6144, False, "strip"), (64, 14336, 11008, False, "rows"), (64, 8192, 8576, False, "rows"),
+    (80, 8192, 4096, False, "strip"), (80, 14336, 2048, False, "rows"), (112, 14336, 2048, False, "strip"),
+    (64, 14336, 6144, False, "rows"), (64, 5120, 13824, False, "rows"), (128, 1920, 35136, False, "strip"),
+    (80, 17280, 4352, True, "strip"), (33, 28672, 2048, True, "strip"), (96, 28672, 1024, True, "rows"),
+    (28, 8192, 28672, True, "rows"), (17, 12288, 16512, True, "strip"), (24, 8192, 16512, True, "strip"),
+    (24, 4096, 20480, True, "rows"), (17, 4096, 16512, True, "strip"), (20, 2560, 16512, True, "rows"),
+    (17, 4096, 28672, False, "strip"), (24, 4096, 24576, False, "rows"), (24, 8192, 16512, False, "strip"),
+    (32, 8192, 28672, False, "rows"),
+]
+
+
+@pytest.mark.parametrize("M,K,N,outliers,kernel", FASTER)
+def test_rows_kernel_where_it_is_faster(lib, M, K, N, outliers, kernel):
+    tc = _uniform(K, N, 21)
+    assert fq.fq_launch_kernel(M, K, N, tc if outliers else None)["kernel"] == kernel
+    if not outliers:   # a fused call whose Tile-COO is empty runs dense only
+        assert fq.fq_launch_kernel(M, K, N, _coo(0, 0))["kernel"] == kernel
+    # the workspace asked for serves either way
+    need = fq.fq_workspace_bytes(M, K, N)
+    assert fq.fq_launch_kernel(M, K, N, tc if outliers else None, workspace_bytes=need)["kernel"] == kernel
