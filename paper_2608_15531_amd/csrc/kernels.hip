@@ -589,8 +589,9 @@ __global__ void __launch_bounds__(64 * (NW + NWS))
   // own, whose first 16 bytes double as the trash word, written by the
   // scatter only between the stage's read and its next write.  With two
   // blocks and an outlier image the stage (6 or 8 KB) lives in the image,
-  // which is all zero until the scatter: the stage is zeroed again once the
-  // X fragments are read, and the trash word has a place of its own.
+  // which is all zero until the scatter: the stage (the image's first XR
+  // blocks, all of them) is zeroed again once the X fragments are read, and
+  // the trash word has a place of its own.
   constexpr bool kStageInImage = XR >= 6 && KS;
   unsigned char* xst = kStageInImage ? reinterpret_cast<unsigned char*>(bo)
                                      : smem + a.off_xs + size_t(wave) * (1024 * XR);
@@ -900,6 +901,20 @@ __global__ void __launch_bounds__(64 * (NW + NWS))
         load_tile_dense<MB, MODE, NCB, DENSE, XR, BK, GL>(a, op, min(w_lo + i, last), n0, rg[i]);
         __builtin_amdgcn_sched_barrier(0);
       }
+      if (SPARSE && MODE == 1) {
+        // The image starts all zero (where X is staged in it, the first tile's
+        // stage zeroes the part that it used).  The stores, 8 or 16 KB a wave,
+        // come while the dense loads are out and the group loads wait for
+        // tile_indptr: before the dense loads they would hold those up (4096 x 28672
+        // at 16 rows 19.8 us, here 19.2), after the group loads the first tile's
+        // data would wait for them (19.6; 4096 x 4096 at 16 rows 8.3, here 8.1; 27
+        // rows 10.25, here 10.0).
+        uint4* b4 = reinterpret_cast<uint4*>(bo);
+#pragma unroll
+        for (int i = kStageInImage ? XR : 0; i < kImageBlocks; ++i)
+          b4[i * 64 + lane] = uint4{0u, 0u, 0u, 0u};
+        __builtin_amdgcn_sched_barrier(0);
+      }
       if (SPARSE) {
         a.packed = tail.packed;
         a.n_groups = tail.n_groups;
@@ -909,14 +924,6 @@ __global__ void __launch_bounds__(64 * (NW + NWS))
       for (int i = 0; i < D; ++i) {
         issue_sparse(min(w_lo + i, last), rg[i]);
         __builtin_amdgcn_sched_barrier(0);
-      }
-      if (SPARSE && MODE == 1) {
-        // the image starts all zero; its stores come after the first loads,
-        // which they would hold up (a 16-byte LDS store of a wave takes about
-        // 14 cycles of the CU's LDS; Llama-3-8B layer at one row 48.5 -> 47.9 us)
-        uint4* b4 = reinterpret_cast<uint4*>(bo);
-#pragma unroll
-        for (int i = 0; i < kImageBlocks; ++i) b4[i * 64 + lane] = uint4{0u, 0u, 0u, 0u};
       }
       for (int t = w_lo; t < w_hi; t += D) {
 #pragma unroll
