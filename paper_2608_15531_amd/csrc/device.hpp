@@ -52,12 +52,19 @@ __device__ __forceinline__ uint64_t shr64c(uint64_t p) {
   return r;
 }
 
+// VM holds the mask and the bias in vector registers, otherwise the compiler
+// keeps them in scalar ones.  It gains where every code word meets 64 rows
+// (row-block kernel, 4096 x 28672 at 128 rows 67.0 -> 65.9 us, 4096 x 6144 21.5 ->
+// 21.2) and costs the strip kernel's two-block waves (14336 x 4096 at 27 rows 18.8
+// -> 19.1, 4096 x 14336 at 32 rows 16.8 -> 16.9); at up to 16 rows it changes
+// nothing.
+template <bool VM>
 __device__ __forceinline__ void dequant_pair(uint32_t w0, uint32_t w1, bf16x8_t& b0, bf16x8_t& b1) {
-  // in vector registers: a VALU operation with a scalar-register operand takes
-  // 4.2 cycles of the SIMD where one on vector registers takes 2.5 (two waves)
-  uint32_t mask, bias;
-  asm("v_mov_b32 %0, 0x000f000f" : "=v"(mask));
-  asm("v_mov_b32 %0, 0x43004300" : "=v"(bias));
+  uint32_t mask = 0x000F000Fu, bias = 0x43004300u;
+  if constexpr (VM) {
+    asm("v_mov_b32 %0, 0x000f000f" : "=v"(mask));
+    asm("v_mov_b32 %0, 0x43004300" : "=v"(bias));
+  }
   const uint64_t p = (uint64_t(w1) << 32) | w0;
   const uint64_t s4 = shr64c<4>(p), s8 = shr64c<8>(p), s12 = shr64c<12>(p);
   u32x4_t r0, r1;

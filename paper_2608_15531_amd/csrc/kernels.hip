@@ -708,7 +708,7 @@ __global__ void __launch_bounds__(64 * (NW + NWS))
   #pragma unroll
           for (int c = 0; c < NCB; c += 2) {
             bf16x8_t Bq[2];
-            dequant_pair(w4[c], w4[c + 1], Bq[0], Bq[1]);
+            dequant_pair<false>(w4[c], w4[c + 1], Bq[0], Bq[1]);
   #pragma unroll
             for (int e = 0; e < 2; ++e) {
               if constexpr (DV) {

@@ -398,7 +398,7 @@ rows_kernel(const uint32_t* Wq, const uint16_t* scales, const uint32_t* zeros, c
       // columns 2 c4 and 2 c4 + 1 of one packed row -> the two operands
       const auto sw = __builtin_amdgcn_permlane16_swap(r.w[s].x, r.w[s].y, false, false);
       bf16x8_t Bq[2];
-      dequant_pair(sw[0], sw[1], Bq[0], Bq[1]);
+      dequant_pair<true>(sw[0], sw[1], Bq[0], Bq[1]);
 #pragma unroll
       for (int m = 0; m < 2; ++m) {
         if (SPARSE) {
