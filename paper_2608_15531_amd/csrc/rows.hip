@@ -387,7 +387,13 @@ rows_kernel(const uint32_t* Wq, const uint16_t* scales, const uint32_t* zeros, c
       for (int q = 0; q < 16; ++q) tmp[b][q] = 0.f;
     bf16x8_t As[4];
     f32x4_t xsum{0.f, 0.f, 0.f, 0.f};
-    asm volatile("s_barrier" ::: "memory");   // the other group's turn to scale ends here
+    // The other group's turn to scale ends here.  No wait comes with it: of this
+    // wave's LDS reads only those of a tile's first X and image blocks may be out,
+    // which nothing overwrites before the next lds_barrier.  The row sums, which
+    // the next tile overwrites, have been read: their use in the scaling is not
+    // moved past the barrier.
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_barrier" ::: "memory");
     __builtin_amdgcn_s_setprio(1);
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
