@@ -20,8 +20,9 @@ extern "C" {
  * launch to host memory.  Entry [w][0..3] of wave w (workgroup b, wave i of
  * W waves per workgroup: w = b W + i) holds the s_memrealtime counter
  * (100 MHz, device-wide) when the wave started, when the data of its first
- * tile had arrived (0 when it had no tile), when its tile loop ended and when
- * it exited.  Entries of waves the last launch did not have keep older
+ * tile had arrived (0 when it had no tile; in the row-block kernel, when its K
+ * group's first X slice and outlier groups were in LDS), when its tile loop
+ * ended and when it exited.  Entries of waves the last launch did not have keep older
  * values.  Synchronise the launch's stream first.
  *   host     uint64 [n_waves][4] (host memory)
  *   n_waves  1 .. 8192

@@ -112,6 +112,12 @@ int launch_rows(const Plan& plan, const MatmulPtrs& p, bool sparse, bool two_gro
                 void* stream);
 size_t rows_lds_bytes(const Plan& plan);
 
+#ifdef FQ_WAVE_STAMPS
+// Instrumented build: the current device's stamps, kMaxStampWaves x 4 (null: none).
+constexpr int kMaxStampWaves = 8192;
+uint64_t* wave_stamps_address();
+#endif
+
 // Enqueues one matmul kernel; returns a hipError_t value (0 on success).
 int launch_matmul(const Plan& plan, const MatmulPtrs& p, bool dense, bool sparse, void* stream);
 

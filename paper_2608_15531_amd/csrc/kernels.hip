@@ -65,7 +65,7 @@ namespace fqk {
 // Instrumented build (libfq_stamps.so, include/fq_debug.h): every wave of a
 // matmul launch records s_memrealtime (100 MHz) when it starts, when its first
 // tile's data have arrived, when its tile loop ends and when it exits.
-constexpr int kMaxStampWaves = 8192;
+constexpr int kMaxStampWaves = fqi::kMaxStampWaves;
 __device__ uint64_t g_wave_stamps[kMaxStampWaves][4];
 #endif
 
@@ -1600,6 +1600,12 @@ int launch_decode(const uint32_t* tile_indptr, int64_t n_tiles, const uint32_t* 
 
 #ifdef FQ_WAVE_STAMPS
 #include "fq_debug.h"
+
+uint64_t* fqi::wave_stamps_address() {
+  void* p = nullptr;
+  return hipGetSymbolAddress(&p, HIP_SYMBOL(fqk::g_wave_stamps)) == hipSuccess
+             ? static_cast<uint64_t*>(p) : nullptr;
+}
 
 extern "C" int fq_debug_wave_stamps(uint64_t* host, int64_t n_waves) {
   if (!host || n_waves < 1 || n_waves > fqk::kMaxStampWaves) return 1;

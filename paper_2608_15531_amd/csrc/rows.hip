@@ -75,7 +75,25 @@ struct RowsTail {
   void* Y;
   float* partials;
   uint32_t* counters;
+#ifdef FQ_WAVE_STAMPS
+  uint64_t* stamps;
+#endif
 };
+
+#ifdef FQ_WAVE_STAMPS
+// A wave's start, its first tile's X and groups in LDS, its last turn's end, its exit.
+__device__ __forceinline__ void store_stamps(const RowsTail& tail, int tid, uint64_t s0, uint64_t s1,
+                                             uint64_t s2) {
+  const uint64_t s3 = __builtin_amdgcn_s_memrealtime();
+  const uint32_t w = blockIdx.x * uint32_t(kCW * kKG) + uint32_t(tid >> 6);
+  if ((tid & 63) == 0 && tail.stamps && w < uint32_t(fqi::kMaxStampWaves)) {
+    tail.stamps[4 * w] = s0;
+    tail.stamps[4 * w + 1] = s1;
+    tail.stamps[4 * w + 2] = s2;
+    tail.stamps[4 * w + 3] = s3;
+  }
+}
+#endif
 
 // LDS layout, bytes, one 64 KB page per K group: the group's images, the
 // waves' trash words, its row sums and its first X buffer (image and trash of
@@ -160,6 +178,9 @@ rows_kernel(const uint32_t* Wq, const uint16_t* scales, const uint32_t* zeros, c
             const uint32_t* tile_indptr, int M_all, int K, int N, int GS, RowsTail tail) {
   typedef RowsLds<RB> L;
   extern __shared__ __align__(16) unsigned char smem[];
+#ifdef FQ_WAVE_STAMPS
+  const uint64_t stamp0 = __builtin_amdgcn_s_memrealtime();
+#endif
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -455,6 +476,9 @@ rows_kernel(const uint32_t* Wq, const uint16_t* scales, const uint32_t* zeros, c
   // The K groups run half a tile apart: while one multiplies, the other, on
   // the same SIMDs, stages, scatters and scales.
   lds_barrier();   // the first X slices
+#ifdef FQ_WAVE_STAMPS
+  const uint64_t stamp1 = __builtin_amdgcn_s_memrealtime();
+#endif
   fetch(0, 0, 0);
   if (kg == 1) asm volatile("s_barrier" ::: "memory");
   // (pairs of tiles, then an odd last one: no path leads from an even tile to
@@ -466,6 +490,9 @@ rows_kernel(const uint32_t* Wq, const uint16_t* scales, const uint32_t* zeros, c
   }
   if (i < iters) body(i, std::integral_constant<int, 0>{});
   if (kg == 0) asm volatile("s_barrier" ::: "memory");
+#ifdef FQ_WAVE_STAMPS
+  const uint64_t stamp2 = __builtin_amdgcn_s_memrealtime();
+#endif
 
   // ------------------------------------------------------------------ reduce
   const int y_f32 = tail.y_f32;
@@ -525,7 +552,12 @@ rows_kernel(const uint32_t* Wq, const uint16_t* scales, const uint32_t* zeros, c
               uint32_t(lane) * 16u), 0, kSc1);
     }
   }
-  if (S == 1) return;
+  if (S == 1) {
+#ifdef FQ_WAVE_STAMPS
+    store_stamps(tail, tid, stamp0, stamp1, stamp2);
+#endif
+    return;
+  }
   __builtin_amdgcn_s_waitcnt(0);   // this thread's partial stores have completed
   __syncthreads();
   if (tid == 0) {
@@ -560,6 +592,9 @@ rows_kernel(const uint32_t* Wq, const uint16_t* scales, const uint32_t* zeros, c
     if (tid == 0)
       __hip_atomic_store(tail.counters + block, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
+#ifdef FQ_WAVE_STAMPS
+  store_stamps(tail, tid, stamp0, stamp1, stamp2);
+#endif
 }
 
 template <int RB, bool SPARSE, int GL>
@@ -577,6 +612,9 @@ int launch_rows_variant(const fqi::Plan& pl, const fqi::MatmulPtrs& p, hipStream
   tail.Y = p.Y;
   tail.counters = static_cast<uint32_t*>(p.workspace);
   tail.partials = reinterpret_cast<float*>(static_cast<char*>(p.workspace) + fqi::kCounterRegion);
+#ifdef FQ_WAVE_STAMPS
+  tail.stamps = fqi::wave_stamps_address();
+#endif
   const int G = pl.rows_G, S = pl.rows_S;
   hipLaunchKernelGGL(kern, dim3(unsigned(G) * unsigned(pl.rows_blocks)), dim3(64 * kCW * kKG), lds,
                      stream, p.Wq, p.scales, p.zeros, p.X, p.tile_indptr, pl.M, pl.K, pl.N,

@@ -89,3 +89,34 @@ def test_instrumented_build_stamps_and_results(gpu_lib):
     assert (st[:, 3] >= st[:, 2]).all()
     span_us = (st[:, 3].max() - st[:, 0].min()) / 100.0
     assert 0.5 < span_us < 1000.0
+
+
+@pytest.mark.parametrize("M,K,N", [(33, 1792, 16448), (64, 7296, 8192)], ids=["no split", "split 4"])
+def test_instrumented_build_stamps_row_block_kernel(gpu_lib, M, K, N):
+    """The row-block kernel's waves leave stamps of their own: all later than the
+    launch before, in order, and the results are the plain build's."""
+    from synth import make_problem
+    import paper_2608_15531_amd as fq
+    prob = make_problem(M, K, N, frac=0.01, seed=6)
+    X, Wq, s, z = fq.to_device(prob)
+    host = fq.fq_pack_tile_coo(K, N, prob.k, prob.n, prob.v)
+    tc = fq.TileCOODevice(host)
+    c = fq.fq_launch_kernel(M, K, N, host)
+    assert c["kernel"] == "rows"
+    ref = fq.fq_w4a16_outlier_matmul(X, Wq, s, z, tc, y_dtype="f32")
+    torch.cuda.synchronize()
+    saved = fq._lib
+    try:
+        fq.use_instrumented_build()
+        st = []
+        for _ in range(2):
+            y = fq.fq_w4a16_outlier_matmul(X, Wq, s, z, tc, y_dtype="f32")
+            torch.cuda.synchronize()
+            st.append(fq.fq_debug_wave_stamps(c["workgroups"] * c["waves"]).astype(np.int64))
+    finally:
+        fq._lib = saved
+    assert torch.equal(y, ref)
+    first, last = st
+    assert (first[:, 0] > 0).all() and last[:, 0].min() > first[:, 3].max()
+    assert (np.diff(last, axis=1) >= 0).all()
+    assert 0.5 < (last[:, 3].max() - last[:, 0].min()) / 100.0 < 1000.0
