@@ -3,7 +3,8 @@
 Exact-arithmetic inputs: every fp32 sum is exact in any order, so the result
 equals the fp64 oracle bit for bit on sampled columns (the first and last of
 the 32-, 64- and 128-column blocks among them) and, on every column, the strip
-kernel's, which a forced strip width selects.
+kernel's, which a forced strip width selects.  Both kernels give the same bits
+there, so every test asks fq_launch_kernel which one its calls run.
 """
 
 import dataclasses
@@ -17,28 +18,39 @@ from synth import bf16_bits_from_f32, make_exact_problem, make_problem
 
 pytestmark = pytest.mark.gpu
 
-# (M, K, N, outlier share, packing): the kernel runs where every workgroup gets
-# at least 14 tiles; the workgroups are ceil(N / 128) column blocks x 64-row
-# blocks (32-row ones up to 32 rows), split along K to at most 256
+# (M, K, N, outlier share, packing, row blocks, K ranges)
 CASES = [
-    (33, 1792, 16448, 0.02, None),        # 14 tiles, no split, N an odd multiple of 64
-    (64, 7296, 8192, 0.01, None),         # 57 tiles split 4 ways: 14 and 15
-    (65, 1920, 8320, 0.03, "column"),     # two row blocks, 15 tiles (the K groups take 8 and 7)
-    (128, 2176, 8256, 0.06, None),        # more than 64 groups in a tile, last block half empty
-    (96, 14336, 512, 0.0004, None),       # split 16 ways, most tiles empty
-    (17, 1792, 16512, 0.02, None),        # one 32-row block
-    (32, 2048, 16448, 0.05, "column"),    # one full 32-row block, more than 64 groups
-    (40, 16256, 4096, 0.0, None),         # no outliers: the dense-only form
+    (33, 1792, 16448, 0.02, None, 1, 1),        # 14 tiles, no split, N an odd multiple of 64
+    (64, 7296, 8192, 0.01, None, 1, 4),         # 57 tiles split 4 ways: 14 and 15
+    (97, 1920, 8320, 0.03, "column", 2, 1),     # 15 tiles (the K groups take 8 and 7)
+    (128, 2176, 8256, 0.06, None, 2, 1),        # more than 64 groups in a tile, last block half empty
+    (96, 14336, 2048, 0.0004, None, 2, 8),      # two row blocks and a split, most tiles empty
+    (128, 4096, 6144, 0.01, None, 2, 2),        # two full row blocks and a split
+    (17, 1792, 16512, 0.02, None, 1, 1),        # one 32-row block
+    (32, 2048, 16448, 0.05, "column", 1, 1),    # one full 32-row block, more than 64 groups
+    (40, 16256, 4096, 0.01, None, 1, 8),        # 127 tiles split 8 ways: 15 and 16
+    (48, 1792, 16448, 0.0, None, 1, 1),         # no outliers: the dense-only form
+    (80, 14336, 2048, 0.0, None, 2, 8),         # the same, two row blocks and a split
 ]
 
 
-@pytest.mark.parametrize("M,K,N,frac,packing", CASES, ids=[f"rows{i}" for i in range(len(CASES))])
-def test_rows_kernel_bit_exact(gpu_lib, M, K, N, frac, packing):
+@pytest.mark.parametrize("M,K,N,frac,packing,row_blocks,split", CASES,
+                         ids=[f"rows{i}" for i in range(len(CASES))])
+def test_rows_kernel_bit_exact(gpu_lib, M, K, N, frac, packing, row_blocks, split):
     fq = gpu_lib
     p = make_exact_problem(M, K, N, frac=frac, seed=M + N)
     X, Wq, s, z = fq.to_device(p)
     params = {"buckets_per_tile": 16, "group_mode": fq.FQ_GROUP_BY_COLUMN} if packing else None
-    tc = fq.TileCOODevice(fq.fq_pack_tile_coo(K, N, p.k, p.n, p.v, params))
+    host = fq.fq_pack_tile_coo(K, N, p.k, p.n, p.v, params)
+    tc = fq.TileCOODevice(host)
+    c = fq.fq_launch_kernel(M, K, N, host)
+    assert (c["kernel"], c["row_blocks"], c["split_k"]) == ("rows", row_blocks, split)
+    full = host.sizes.max_tile_groups > 64 and host.sizes.n_groups >= 32 * host.sizes.n_tiles
+    assert c["group_loads"] == (0 if frac == 0 else 2 if full else 1)
+    assert fq.fq_launch_kernel(M, K, N, host, workspace_bytes=fq.NOALLOC_SCRATCH_BYTES) == c
+    assert fq.fq_launch_kernel(M, K, N, host, flags=fq.FQ_STRIP_64)["kernel"] == "strip"
+    if frac == 0:
+        assert fq.fq_launch_kernel(M, K, N)["kernel"] == "rows"
     print(f"rows kernel M={M} K={K} N={N} outliers {frac}", flush=True)
     y = fq.fq_w4a16_outlier_matmul(X, Wq, s, z, tc, y_dtype="f32")
     again = fq.fq_w4a16_outlier_matmul(X, Wq, s, z, tc, y_dtype="f32")
@@ -73,6 +85,7 @@ def test_rows_kernel_one_full_tile(gpu_lib, groups):
     p = dataclasses.replace(p, k=k, n=n, v=bf16_bits_from_f32(v.astype(np.float32)))
     host = fq.fq_pack_tile_coo(K, N, p.k, p.n, p.v)
     assert host.sizes.max_tile_groups == groups
+    assert fq.fq_launch_kernel(M, K, N, host)["kernel"] == ("rows" if groups <= 160 else "strip")
     X, Wq, s, z = fq.to_device(p)
     print(f"rows kernel, one tile of {groups} groups", flush=True)
     y = fq.fq_w4a16_outlier_matmul(X, Wq, s, z, fq.TileCOODevice(host), y_dtype="f32")
@@ -89,7 +102,10 @@ def test_rows_kernel_graph_replays(gpu_lib):
     M, K, N = 64, 7296, 8192
     p = make_exact_problem(M, K, N, frac=0.01, seed=3)
     X, Wq, s, z = fq.to_device(p)
-    tc = fq.TileCOODevice(fq.fq_pack_tile_coo(K, N, p.k, p.n, p.v))
+    host = fq.fq_pack_tile_coo(K, N, p.k, p.n, p.v)
+    tc = fq.TileCOODevice(host)
+    c = fq.fq_launch_kernel(M, K, N, host)
+    assert (c["kernel"], c["split_k"]) == ("rows", 4)
     ws = torch.zeros(fq.fq_workspace_bytes(M, K, N), dtype=torch.uint8, device="cuda")
     eager = fq.fq_w4a16_outlier_matmul(X, Wq, s, z, tc, y_dtype="f32", ws=ws)
     torch.cuda.synchronize()
@@ -115,9 +131,12 @@ def test_rows_kernel_small_workspace(gpu_lib):
     M, K, N = 64, 7296, 8192
     p = make_exact_problem(M, K, N, frac=0.01, seed=4)
     X, Wq, s, z = fq.to_device(p)
-    tc = fq.TileCOODevice(fq.fq_pack_tile_coo(K, N, p.k, p.n, p.v))
+    host = fq.fq_pack_tile_coo(K, N, p.k, p.n, p.v)
+    tc = fq.TileCOODevice(host)
     assert fq.fq_workspace_bytes(M, K, N) > 256 * 1024
     small = torch.zeros(256 * 1024, dtype=torch.uint8, device="cuda")   # 64-column strips need no split here
+    assert fq.fq_launch_kernel(M, K, N, host)["kernel"] == "rows"
+    assert fq.fq_launch_kernel(M, K, N, host, workspace_bytes=small.numel())["kernel"] == "strip"
     y = fq.fq_w4a16_outlier_matmul(X, Wq, s, z, tc, y_dtype="f32")
     y_small = fq.fq_w4a16_outlier_matmul(X, Wq, s, z, tc, y_dtype="f32", ws=small)
     torch.cuda.synchronize()
@@ -133,7 +152,9 @@ def test_rows_kernel_kept_workspace_grows(gpu_lib):
     stream = torch.cuda.Stream()
     p = make_problem(M, K, N, frac=0.01, seed=5)
     X, Wq, s, z = fq.to_device(p)
-    tc = fq.TileCOODevice(fq.fq_pack_tile_coo(K, N, p.k, p.n, p.v))
+    host = fq.fq_pack_tile_coo(K, N, p.k, p.n, p.v)
+    tc = fq.TileCOODevice(host)
+    assert fq.fq_launch_kernel(M, K, N, host)["kernel"] == "rows"
     ws = torch.zeros(fq.fq_workspace_bytes(M, K, N), dtype=torch.uint8, device="cuda")
     full = fq.fq_w4a16_outlier_matmul(X, Wq, s, z, tc, y_dtype="f32", ws=ws)
     torch.cuda.synchronize()
