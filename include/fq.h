@@ -303,6 +303,11 @@ enum { FQ_DENSE_VALU = 128 };
  * every call returns the counters to zero, so no per-call clearing is needed
  * and one workspace may serve problems of any shape in turn.  Calls that may
  * overlap in time need separate workspaces.
+ * A smaller workspace is accepted where it holds the partial sums of the strip
+ * kernel's launch (fq_launch_kernel): with more than 16 rows that kernel then
+ * runs also where the row-block kernel would have, slower and with its own
+ * order of summation, so the result may differ in rounding from that of a call
+ * with a workspace of this size.  Below that: FQ_ERR_WORKSPACE.
  */
 fq_status fq_workspace_bytes(const fq_problem* pr, size_t* bytes);
 
@@ -365,7 +370,8 @@ fq_status fq_launch_config(const fq_problem* pr, int32_t buckets_per_tile, int32
  *   tc                     device Tile-COO with k_tile 128, n_tile 64,
  *                          buckets_per_tile in 1..256.
  *   Y                      device output [M][N]; 16-byte aligned.
- *   workspace              device buffer of at least fq_workspace_bytes().
+ *   workspace              device buffer of fq_workspace_bytes() or more (see there
+ *                          for what a smaller one does).
  *   stream                 hipStream_t (NULL: the default stream).
  * X must be finite.  Malformed Tile-COO contents cannot make the kernel read or
  * write out of bounds (indices are masked and ranges clamped) but give
@@ -383,7 +389,8 @@ fq_status fq_w4a16_outlier_matmul(const fq_problem* pr, const uint16_t* X, const
  * workspace argument and without any device allocation, for callers that
  * cannot allocate: code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc.  Same arguments (minus the workspace),
- * same kernels, same launch plan and the same result bit for bit.
+ * same kernels, same launch plan and the same result bit for bit as with a
+ * workspace of fq_workspace_bytes().
  * The workspace is a static device array of the library, FQ_NOALLOC_SCRATCH_BYTES
  * (256 KiB of arrival counters plus 8 MiB of split-K partial sums), one copy per
  * device, held until the process ends.  A problem whose launch plan needs

@@ -732,3 +732,25 @@ def test_rows_kernel_where_it_is_faster(lib, M, K, N, outliers, kernel):
     # the workspace asked for serves either way
     need = fq.fq_workspace_bytes(M, K, N)
     assert fq.fq_launch_kernel(M, K, N, tc if outliers else None, workspace_bytes=need)["kernel"] == kernel
+
+
+@pytest.mark.parametrize("M,K,N", [(64, 7296, 8192), (128, 14336, 4096), (27, 4096, 28672),
+                                   (16, 14336, 4096)])
+def test_workspace_sizes(lib, M, K, N):
+    """fq_workspace_bytes serves the kernel that the planner picks; down to the
+    strip kernel's partial sums that kernel runs; below, FQ_ERR_WORKSPACE."""
+    tc = _uniform(K, N, 21)
+    need = fq.fq_workspace_bytes(M, K, N)
+    best = fq.fq_launch_kernel(M, K, N, tc)
+    assert fq.fq_launch_kernel(M, K, N, tc, workspace_bytes=need) == best
+    strip = fq.fq_launch_config(M, K, N)
+    part = 0
+    if strip["split_k"] > 1:
+        part = (strip["workgroups"] * 32 * strip["strip_cols"] * 4)
+    small = 256 * 1024 + part
+    c = fq.fq_launch_kernel(M, K, N, tc, workspace_bytes=small)
+    assert c["kernel"] == ("strip" if small < 256 * 1024 + 1024 * best["partial_kib"] or M <= 16
+                           else best["kernel"])
+    with pytest.raises(fq.FqError) as e:
+        fq.fq_launch_kernel(M, K, N, tc, workspace_bytes=min(small, 256 * 1024 + 1024 * best["partial_kib"]) - 1)
+    assert e.value.name == "FQ_ERR_WORKSPACE"
