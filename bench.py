@@ -24,6 +24,7 @@ import json
 import os
 import sys
 import time
+import types
 
 import numpy as np
 
@@ -53,35 +54,29 @@ GEMM_CANDIDATES = 16
 GEMM_WORKSPACE = 64 << 20
 
 
-def rows_kernel_split(M, K, N):
-    """K ranges per column block where the row-block kernel takes the call (its
-    planner's rule, for matrices without very full tiles), else 0: more than 16
-    rows and at least 14 tiles of K per workgroup of 128 columns x 64 (32) rows;
-    no split up to 32 rows; rounds of workgroups filled."""
-    if M <= 16:
-        return 0
-    rows = 32 if M <= 32 else 64
-    units = -(-N // 128) * -(-M // rows)
-    split = max(1, 256 // units)
-    if rows == 32 and split > 1:
-        return 0
-    split = max(split, -(-(K // 128) // 126))
-    rounds = -(-units * split // 256)
-    if rounds > 1 and rows == 32:
-        return 0
-    if rounds > 1 and units * split / (256 * rounds) * M / (rows * -(-M // rows)) < 0.65:
-        return 0
-    return split if K // 128 // split >= 14 else 0
+def launch_of(fq, M, K, N, packing=None, flags=0, sizes=None):
+    """fq_launch_kernel's answer for a Tile-COO packed with `packing` (default: the
+    library default), whose sizes are `sizes` (default: a 1 % matrix's, 21 groups
+    a tile by bucket, 47 by column)."""
+    params = fq.load().fq_default_tilecoo_params()
+    for key, value in (packing or {}).items():
+        setattr(params, key, value)
+    if sizes is None:
+        sizes = fq.fq_tilecoo_sizes()
+        per_tile = 47 if params.group_mode == fq.FQ_GROUP_BY_COLUMN else 21
+        sizes.n_groups, sizes.max_tile_groups = K // 128 * (N // 64) * per_tile, per_tile + 10
+    return fq.fq_launch_kernel(M, K, N, types.SimpleNamespace(params=params, sizes=sizes), flags=flags)
 
 
 def kernel_name(fq, M, K, N, packing=None, flags=0, sizes=None):
     """Template instance of the fused kernel the library launches for (M, K, N),
     a Tile-COO packed with `packing` (default: the library default) and the
-    switches `flags`; `sizes`: the Tile-COO's, where its tiles may be full."""
+    switches `flags`; `sizes`: the Tile-COO's (default: a 1 % matrix's)."""
     packing = packing or {}
-    gl = 2 if sizes and sizes.max_tile_groups > 64 and sizes.n_groups >= 32 * sizes.n_tiles else 1
-    if not flags and rows_kernel_split(M, K, N):
-        return f"rows_kernel<{1 if M <= 32 else 2}, true, {gl}>"
+    launch = launch_of(fq, M, K, N, packing, flags, sizes)
+    gl = max(1, launch["group_loads"])
+    if launch["kernel"] == "rows":
+        return f"rows_kernel<{launch['block_rows'] // 32}, true, {gl}>"
     c = fq.fq_launch_config(M, K, N, buckets_per_tile=packing.get("buckets_per_tile"),
                             group_mode=packing.get("group_mode"), flags=flags)
     mb = 1 if min(M, 32) <= 16 else 2
@@ -620,12 +615,12 @@ def mfma_flops(fq, M, K, N):
     row-block kernel, per 32 columns and tile, 8 dense and 8 image MFMAs of
     32 x 32 x 16 for each 32-row block and 4 row-sum MFMAs; its two K groups
     walk equally many tiles, the shorter one its last tile twice."""
-    split = rows_kernel_split(M, K, N)
-    if split:
-        rb = 1 if M <= 32 else 2
+    launch = launch_of(fq, M, K, N)
+    if launch["kernel"] == "rows":
+        split, rb = launch["split_k"], launch["block_rows"] // 32
         T = K // 128
         tiles = sum(2 * -(-((i + 1) * T // split - i * T // split) // 2) for i in range(split))
-        waves = 4 * -(-N // 128) * -(-M // (32 * rb))
+        waves = 4 * -(-N // 128) * launch["row_blocks"]
         return waves * tiles * (16 * rb * 32 * 32 * 16 + 4 * 16 * 16 * 32) * 2
     c = fq.fq_launch_config(M, K, N)
     ncb = c["strip_cols"] // 16

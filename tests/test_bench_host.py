@@ -1,13 +1,14 @@
 """Host-side pieces of bench.py that need no GPU: the dense bf16 weight the
 bf16 GEMM comparator reads, bf16(dequant(W_Q) + W_O) (eq. 1 and eq. 3),
 checked bit for bit against the oracle's dequantisation on the same
-synthetic problem."""
+synthetic problem; the kernel names of the records."""
 
 import numpy as np
 import torch
 
 import bench
 import oracle
+import paper_2608_15531_amd as fq
 from synth import make_problem
 
 
@@ -26,3 +27,27 @@ def test_comparator_weight_matches_oracle():
     assert np.array_equal(got, want)
     # an outlier position holds exactly the outlier (its code is the zero-point)
     assert np.array_equal(got[p.k, p.n], p.v)
+
+
+def _sizes(K, N, per_tile, fullest):
+    s = fq.fq_tilecoo_sizes()
+    s.n_groups, s.max_tile_groups = K // 128 * (N // 64) * per_tile, fullest
+    return s
+
+
+def test_kernel_names_follow_the_launch():
+    assert bench.kernel_name(fq, 128, 4096, 28672) == "rows_kernel<2, true, 1>"
+    # one tile beyond the row-block kernel's groups; partial sums beyond the scratch
+    assert bench.kernel_name(fq, 128, 4096, 28672, sizes=_sizes(4096, 28672, 21, 161)).startswith("matmul_kernel<2, 1")
+    assert bench.kernel_name(fq, 64, 28672, 28672).startswith("matmul_kernel<2, 1")
+    # a second group load only where the instance exists
+    full = _sizes(4096, 28672, 103, 124)
+    assert bench.kernel_name(fq, 8, 4096, 28672, sizes=full).endswith("2>")
+    for flags in (fq.FQ_SCHED_STREAM_K, fq.FQ_SPARSE_WAVES):
+        assert bench.kernel_name(fq, 8, 4096, 28672, flags=flags, sizes=full).endswith("1>")
+    assert bench.kernel_name(fq, 1, 4096, 28672, flags=fq.FQ_DENSE_VALU, sizes=full).endswith("1>")
+    by_column = {"group_mode": fq.FQ_GROUP_BY_COLUMN, "buckets_per_tile": 16}
+    assert bench.kernel_name(fq, 1, 4096, 28672, packing=by_column, sizes=full).endswith("1>")
+    # FLOPs of the row-block kernel: 4 column waves x 224 column blocks x 2 row blocks, 32
+    # tiles, 32 MFMAs of 32 x 32 x 16 and 4 of 16 x 16 x 32 each
+    assert bench.mfma_flops(fq, 128, 4096, 28672) == 4 * 224 * 2 * 32 * (32 * 16384 + 4 * 8192) * 2
