@@ -13,8 +13,8 @@ value = algorithmic bytes of the step / step time, in GB/s, where the bytes
 of one matmul are INT4 codes + fp16 scales + INT4 zero-points + stored
 Tile-COO bytes (padding included) + X + Y.
 
-Prints ONE JSON line (the contract) and, with --details, a per-matmul table
-to stderr.
+Prints ONE JSON line (the contract) with the time of every matmul; with
+--details a per-matmul table on stderr, with --details-file every record.
 """
 
 from __future__ import annotations
@@ -87,6 +87,25 @@ def kernel_name(fq, M, K, N, packing=None, flags=0, sizes=None):
     dv = "true" if flags & fq.FQ_DENSE_VALU else "false"
     return (f"matmul_kernel<{mb}, {mode}, {c['strip_cols'] // 16}, true, true, "
             f"{c['dense_waves']}, {sk}, {c['outlier_waves']}, {xs}, {bk}, {dv}, {gl}>")
+
+
+def contract_line(result):
+    """The one JSON line: the whole result but for the per-matmul records, of
+    which it keeps the times (us), and the comparator's description.  Kernel names
+    and every other field are in --details-file."""
+    line = {k: v for k, v in result.items() if k not in ("per_matmul", "bf16_gemm_comparator", "pack_s")}
+    for key, field in (("fused_us", "fused_us"), ("unfused_us", "unfused_us"),
+                       ("dense_only_us", "dense_only_us"), ("bf16_gemm_us", "bf16_gemm_us")):
+        times = {f"{d['shape']}/M{d['M']}": round(d[field], 2) for d in result["per_matmul"] if field in d}
+        if times:
+            line[key] = times
+    if line.get("tilecoo_paper_format"):
+        line["tilecoo_paper_format"] = {k: line["tilecoo_paper_format"][k]
+                                        for k in ("ms_per_step", "value", "unit", "default_speedup")}
+    if "cpu_baseline" in line:
+        line["cpu_baseline"] = {k: v for k, v in line["cpu_baseline"].items()
+                                if k in ("value", "unit", "cores", "kind", "cpu_model")}
+    return line
 
 
 def dominant_kernel(fq, cases):
@@ -1706,6 +1725,8 @@ def main():
     ap.add_argument("--no-compare", action="store_true",
                     help="skip the unfused / dense-only / hipBLASLt comparison table")
     ap.add_argument("--details", action="store_true", help="per-matmul table on stderr")
+    ap.add_argument("--details-file", metavar="JSON",
+                    help="the whole result (per-matmul records, the comparator's kernels) as a file")
     ap.add_argument("--ablation", action="store_true",
                     help="no step timing: per-matmul times of the unfused baseline and of the "
                          "fused kernel with its techniques added one by one (SD: fused; EW: "
@@ -2124,7 +2145,10 @@ def main():
     if args.details:
         for d in details:
             log(json.dumps(d))
-    print(json.dumps(result), flush=True)
+    if args.details_file:
+        with open(args.details_file, "w") as fh:
+            json.dump(result, fh, indent=1)
+    print(json.dumps(contract_line(result)), flush=True)
 
 if __name__ == "__main__":
     main()

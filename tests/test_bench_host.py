@@ -1,7 +1,9 @@
 """Host-side pieces of bench.py that need no GPU: the dense bf16 weight the
 bf16 GEMM comparator reads, bf16(dequant(W_Q) + W_O) (eq. 1 and eq. 3),
 checked bit for bit against the oracle's dequantisation on the same
-synthetic problem; the kernel names of the records."""
+synthetic problem; the kernel names of the records; the length of the JSON line."""
+
+import json
 
 import numpy as np
 import torch
@@ -51,3 +53,27 @@ def test_kernel_names_follow_the_launch():
     # FLOPs of the row-block kernel: 4 column waves x 224 column blocks x 2 row blocks, 32
     # tiles, 32 MFMAs of 32 x 32 x 16 and 4 of 16 x 16 x 32 each
     assert bench.mfma_flops(fq, 128, 4096, 28672) == 4 * 224 * 2 * 32 * (32 * 16384 + 4 * 8192) * 2
+
+
+def test_json_line_is_short():
+    """The line holds the contract's fields and every matmul's time, and stays
+    below 3000 characters whatever the library kernels' names are."""
+    details = [{"shape": name, "M": M, "K": K, "N": N, "kernel": "k" * 80, "bf16_gemm_kernel": "Cijk_" * 90,
+                "fused_us": 12.345, "unfused_us": 23.456, "dense_only_us": 10.123, "bf16_gemm_us": 34.567}
+               for name, K, N in bench.SHAPES for M in bench.MS]
+    fields = {"metric": bench.METRIC, "value": 2700.12, "unit": "GB/s", "n_gpus": 1, "steps": 200,
+              "warmup": 20, "ms_per_step": 0.18, "higher_is_better": True, "scaling": "weak",
+              "vs_baseline": None, "dtype": "bf16", "data": "synthetic", "config": {"workload": "w" * 400},
+              "roofline": {"kernel": "k" * 80, "launches": ["gate_up/M1"] * 8}}
+    result = dict(fields, per_matmul=details, pack_s={"qkv": 0.1}, bf16_gemm_comparator="c" * 400,
+                  layer_aggregate=[{"M": M, "bytes": 116000000, "fused_us": 41.234, "GBs": 2800.1,
+                                    "pct_peak": 35.1, "pct_of_probe": 50.2} for M in bench.MS],
+                  tilecoo_paper_format={"tilecoo": "t" * 90, "ms_per_step": 0.18, "value": 2800.1,
+                                        "unit": "GB/s", "step_bytes": 1, "us_per_matmul": 1,
+                                        "default_speedup": 1.01},
+                  cpu_baseline={"value": 0.0055, "unit": "GB/s", "cores": 16, "kind": "oracle",
+                                "cpu_model": "x", "sample": "s" * 300, "per_case": [{"case": "c" * 40}] * 8})
+    line = bench.contract_line(result)
+    assert all(line[k] == v for k, v in fields.items())
+    assert set(line["fused_us"]) == {f"{n}/M{M}" for n, _, _ in bench.SHAPES for M in bench.MS}
+    assert len(json.dumps(line)) < 3000
