@@ -1345,9 +1345,9 @@ def strip_load_probe(fq, torch, dev, R: int = 8):
 
 def launch_timeline(torch, dev, R: int = 8):
     """Markdown on stdout: where a fused launch's time goes, per wave, from the
-    instrumented build (libfq_stamps.so): each Llama-3-8B decode matmul in a
-    graph of 4 R launches over R rotated weight copies, the last launch's
-    stamps after replays, median of 5."""
+    instrumented build (libfq_stamps.so): each Llama-3-8B decode matmul, and those
+    at 64 and 128 rows that the row-block kernel takes, in a graph of 4 R launches
+    over R rotated weight copies, the last launch's stamps after replays, median of 5."""
     import paper_2608_15531_amd as fq
     from synth import make_activations, make_problem, seed_for
     fq.use_instrumented_build()
@@ -1356,28 +1356,32 @@ def launch_timeline(torch, dev, R: int = 8):
            "    python3 -u bench.py --launch-timeline > profiles/launch_timeline.md", "",
            "The instrumented build `libfq_stamps.so` (include/fq_debug.h: the same kernels with "
            "four `s_memrealtime` stamps per wave) runs each Llama-3-8B decode matmul (default "
-           "packing, 1 % outliers) in a graph of 32 launches over 8 rotated weight copies; after "
+           "packing, 1 % outliers), and at 64 and 128 rows those that the row-block kernel takes, "
+           "in a graph of 32 launches over 8 rotated weight copies; after "
            "warm replays the last launch's stamps are read.  Times in us from the first wave's "
            "start: `start` = when a wave began (median / max over waves), `first data` = from "
            "its start until its first tile's loads had arrived, `loop` = its tile loop, "
            "`epilogue` = from the loop's end to its exit (the workgroup barrier, the reduction "
            "across waves and, under split-K, across workgroups), `end` = its exit (median / max: "
            "the max is the kernel's span).  `launch` = HIP-event time per launch of the graph "
-           "(the span plus the dispatch gap).  Medians over 5 replays.", "",
+           "(the span plus the dispatch gap).  `turn` (row-block kernel) = the loop over its "
+           "turns, one more than two for each tile of a K group.  Medians over 5 replays.", "",
            "| matmul | waves | launch us | start med / max | first data | loop | epilogue "
-           "(med / p90) | end med / max |", "|---|---|---|---|---|---|---|---|"]
+           "(med / p90) | end med / max | turn |", "|---|---|---|---|---|---|---|---|---|"]
     ws = torch.zeros(64 << 20, dtype=torch.uint8, device=dev)
     for si, (name, K, N) in enumerate(SHAPES):
         p = make_problem(1, K, N, frac=FRAC, seed=seed_for(1, si, 0))
         host = fq.fq_pack_tile_coo(K, N, p.k, p.n, p.v)
         W = [fq.to_device(p, dev)[1:] for _ in range(R)]
         T = [fq.TileCOODevice(host, dev) for _ in range(R)]
-        for mi, M in enumerate(MS):
+        for mi, M in enumerate(MS + [64, 128]):
+            launch = fq.fq_launch_kernel(M, K, N, host)
+            if M > 16 and launch["kernel"] != "rows":
+                continue
             x = torch.from_numpy(make_activations(M, K, seed_for(1, si, mi)).view(np.int16)
                                  .copy()).view(torch.bfloat16).to(dev)
             Y = torch.empty((M, N), dtype=torch.bfloat16, device=dev)
-            c = fq.fq_launch_config(M, K, N)
-            nw = c["workgroups"] * (c["dense_waves"] + c["outlier_waves"])
+            nw = launch["workgroups"] * launch["waves"]
             L = 4 * R
             g = capture_graph(torch, lambda: [fq.fq_w4a16_outlier_matmul(
                 x, *W[i % R], T[i % R], Y=Y, ws=ws) for i in range(L)])
@@ -1395,9 +1399,11 @@ def launch_timeline(torch, dev, R: int = 8):
                              np.median(epi), np.percentile(epi, 90), np.median(end), end.max()])
             del g
             m = np.median(np.array(rows), axis=0)
+            turns = 2 * -(-(-(-(K // 128) // launch["split_k"])) // 2) + 1
+            turn = f"{m[4] / turns:.3f}" if launch["kernel"] == "rows" else "-"
             out.append(f"| {name}/M{M} | {nw} | {m[0]:.2f} | {m[1]:.2f} / {m[2]:.2f} | "
                        f"{m[3]:.2f} | {m[4]:.2f} | {m[5]:.2f} / {m[6]:.2f} | "
-                       f"{m[7]:.2f} / {m[8]:.2f} |")
+                       f"{m[7]:.2f} / {m[8]:.2f} | {turn} |")
         del W, T
         torch.cuda.empty_cache()
     print("\n".join(out))
