@@ -22,9 +22,11 @@ constexpr int kImageBytes = 16384;   // one wave's B-operand image of a 128 x 64
 constexpr size_t kCounterRegion = 256 * 1024;
 constexpr int kMaxStrips = int(kCounterRegion / 4);
 // Static device scratch of the allocation-free entry point: the counter
-// region followed by room for the split-K partial sums (8 MiB: every launch
-// plan of the Llama-3-8B/-70B decode and larger-M workloads needs at most
-// 4 MiB of them).
+// region followed by 8 MiB of split-K partial sums.  On the Llama-3-8B and -70B
+// linears the strip kernel needs up to 4 MiB of them, the row-block kernel all
+// 8 (14336 x 4096 above 32 rows): where it splits, its 256 workgroups of 32 KiB
+// each are that much, and a launch that would need more is not made
+// (kRowsPartialLimit).
 constexpr size_t kScratchBytes = kCounterRegion + (size_t(8) << 20);
 
 // The row-block kernel (rows.hip) serves more rows than this, with at least so
@@ -35,9 +37,10 @@ constexpr double kRowsMinFill = 0.65; // of the rounds of workgroups, with more 
 constexpr int kRowsMaxGroups = 160;   // of the largest tile
 constexpr size_t kRowsPartialLimit = kScratchBytes - kCounterRegion;
 
-// Launch plan of one matmul kernel.  Everything that sizes the workspace
-// depends only on (M, K, N, split_k) so the workspace can be sized before the
-// Tile-COO exists.
+// Launch plan of one matmul kernel.  The Tile-COO decides between the kernels,
+// but no launch needs more workspace than fq_workspace_bytes finds from
+// (M, K, N, split_k) alone, so the workspace can be sized before the Tile-COO
+// exists.
 struct Plan {
   int M, K, N;
   int MB;            // 16-row MFMA blocks per slab: 1 (M <= 16) or 2

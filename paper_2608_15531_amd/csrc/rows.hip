@@ -34,17 +34,19 @@
 //             register order with device-coherent stores and the last to
 //             arrive at the block's counter adds them in split order.
 //
-// What bounds it: the issue of one wave's turn.  At 128 rows a turn takes about
-// 2000 cycles: 1100 of MFMA, and LDS reads, waits and the other instructions that
-// do not fit between them (time stamps at the barriers).
-// Per call against the strip kernel (1 % outliers, graph replay, rotated weights):
-//   4096 x 28672  128 rows 79.8 -> 68.1 us, 64 rows 49.0 -> 37.8, 27 rows 28.8 -> 27.0
-//   4096 x 14336  128 rows 47.2 -> 34.2 us, 64 rows 27.7 -> 23.5, 40 rows 27.0 -> 23.7
-//   14336 x 4096  128 rows 40.6 -> 35.1 us, 64 rows 27.6 -> 26.0
-//   4096 x 6144   128 rows 26.0 -> 22.8 us
+// What bounds it: the issue of one wave's turn.  With 64 rows a turn takes 0.76
+// to 0.83 us (the instrumented build's tile loop over its turns), about 2000
+// cycles at 2.4 GHz: 1088 of MFMA (32 of 32 cycles, 4 of 16), and LDS reads, waits
+// and the other instructions that do not fit between them.
+// Per call, strip kernel -> this one (1 % outliers, graph replay, rotated weights,
+// both in turn in one process):
+//   4096 x 28672  128 rows 79.1 -> 65.1 us, 64 rows 47.6 -> 34.1, 27 rows 27.3 -> 24.8
+//   4096 x 14336  128 rows 45.8 -> 33.1 us, 64 rows 26.0 -> 22.2, 40 rows 25.2 -> 21.8
+//   14336 x 4096  128 rows 39.6 -> 33.6 us, 64 rows 25.7 -> 23.6
+//   4096 x 6144   128 rows 24.8 -> 21.4 us
 // With two group loads per tile (5 % outliers): 4096 x 14336 at 128 rows
-// 58.0 -> 39.8 us, at 64 rows 33.4 -> 27.1.
-// Tried and slower (4096 x 14336 at 128 rows, 34.1 us): 16x16x32 MFMAs 38.2 us
+// 49.0 -> 37.2 us, at 64 rows 27.7 -> 24.7.
+// Tried and slower (4096 x 14336 at 128 rows, 34.1 us then): 16x16x32 MFMAs 38.2 us
 // with scalar-unit masks in the scatter; tile_indptr by scalar loads, which every
 // LDS wait then waits for, 39.0 us; all loads and the scatter's addresses among
 // the MFMAs 39.0 us; X stored one step later or earlier 34.8 and 36.0 us; LDS
@@ -687,11 +689,11 @@ static bool rows_faster(const Plan& p, int rb, int blocks, int S, int64_t units,
 // It takes the calls that rows_faster gives it, where every workgroup has at
 // least kRowsMinTiles tiles: below, its start (two tiles of loads, an LDS exchange)
 // and the partial sums of the larger blocks cost more than the shared work
-// saves (64 rows: 14336 x 4096, 14 tiles, 26.0 against 27.6 us; 4096 x 6144, 6
+// saves (64 rows: 14336 x 4096, 14 tiles, 23.6 against 25.7 us; 4096 x 6144, 6
 // tiles, 17.4 against 16.7; 4096 x 4096, 4 tiles, 16.9 against 13.9.  128 rows:
-// 4096 x 4096, 8 tiles, 17.8 against 16.8; 4096 x 6144, 16 tiles, 22.8 against
-// 26.0).  Up to 32 rows only without a split (27 rows: 4096 x 28672 27.0 against
-// 28.8 us, 4096 x 14336 split 2 18.6 against 18.5).
+// 4096 x 4096, 8 tiles, 17.8 against 16.8; 4096 x 6144, 16 tiles, 21.4 against
+// 24.8).  Up to 32 rows only without a split (27 rows: 4096 x 28672 24.8 against
+// 27.3 us, 4096 x 14336 split 2 18.6 against 18.5).
 // A matrix with a tile of more than kRowsMaxGroups groups is left to the strip
 // kernel, whose waves do not wait for one another at every tile (5 % outliers,
 // half in 2 % of the columns, over 200 groups in a tile: 4096 x 28672 at 27 rows
@@ -699,8 +701,8 @@ static bool rows_faster(const Plan& p, int rb, int blocks, int S, int64_t units,
 // 150 groups, at 64 rows: 26.7 against 32.1).
 // More than one round of workgroups has to be filled, in CUs and rows together, by
 // kRowsMinFill (4096 x 38400 at 64 rows, 300 workgroups, 0.59: 68.9 against 62.6 us;
-// 4096 x 28672 at 80 rows, 0.55: 67.6 against 67.7, at 128 rows, 0.88: 68.1 against
-// 79.8); up to 32 rows only a single round gains (8192 x 57344 at 32 rows 98.4
+// 4096 x 28672 at 80 rows, 0.55: 67.6 against 67.7, at 128 rows, 0.88: 65.1 against
+// 79.1); up to 32 rows only a single round gains (8192 x 57344 at 32 rows 98.4
 // against 97.2).
 // Partial sums beyond kRowsPartialLimit are left to the strip kernel, so that
 // every default launch fits the static scratch.
