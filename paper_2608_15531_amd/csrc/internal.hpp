@@ -34,7 +34,8 @@ constexpr size_t kScratchBytes = kCounterRegion + (size_t(8) << 20);
 constexpr int kRowsMinM = 16;
 constexpr int kRowsMinTiles = 14;
 constexpr double kRowsMinFill = 0.65; // of the rounds of workgroups, with more than one
-constexpr int kRowsMaxGroups = 160;   // of the largest tile
+constexpr int kRowsMaxGroups = 160;   // of the largest tile, with 64-row blocks
+constexpr int kRowsMaxGroups32 = 64;  // the same with 32-row blocks: one load's worth
 constexpr size_t kRowsPartialLimit = kScratchBytes - kCounterRegion;
 
 // Launch plan of one matmul kernel.  The Tile-COO decides between the kernels,

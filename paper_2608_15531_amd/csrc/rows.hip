@@ -44,7 +44,7 @@
 //   4096 x 14336  128 rows 45.8 -> 33.1 us, 64 rows 26.0 -> 22.2, 40 rows 25.2 -> 21.8
 //   14336 x 4096  128 rows 39.6 -> 33.6 us, 64 rows 25.7 -> 23.6
 //   4096 x 6144   128 rows 24.8 -> 21.4 us
-// With two group loads per tile (5 % outliers): 4096 x 14336 at 128 rows
+// With two group loads per tile (64 rows only; 5 % outliers): 4096 x 14336 at 128 rows
 // 49.0 -> 37.2 us, at 64 rows 27.7 -> 24.7.
 // Tried and slower (4096 x 14336 at 128 rows, 34.1 us then): 16x16x32 MFMAs 38.2 us
 // with scalar-unit masks in the scatter; tile_indptr by scalar loads, which every
@@ -696,9 +696,14 @@ static bool rows_faster(const Plan& p, int rb, int blocks, int S, int64_t units,
 // 27.3 us, 4096 x 14336 split 2 18.6 against 18.5).
 // A matrix with a tile of more than kRowsMaxGroups groups is left to the strip
 // kernel, whose waves do not wait for one another at every tile (5 % outliers,
-// half in 2 % of the columns, over 200 groups in a tile: 4096 x 28672 at 27 rows
-// 67.7 against 45.6 us, 4096 x 14336 at 128 rows 70.7 against 62.7; 2 %, 100 to
-// 150 groups, at 64 rows: 26.7 against 32.1).
+// half in 2 % of the columns, over 200 groups in a tile: 4096 x 14336 at 128 rows
+// 70.7 against 62.7 us; 2 %, 100 to 150 groups, at 64 rows: 26.7 against 32.1).  With
+// 32-row blocks, whose turns are too short to cover a second load or the wait of a
+// fuller tile, already one of more than kRowsMaxGroups32 (3 %, up to 79 groups: 3328 x
+// 25792 at 17 rows 27.0 against 23.4, 4096 x 28672 at 32 rows 32.4 against 30.1; 5 %:
+// 26.9 against 23.8, 32.8 against 31.5; 2 %, half in 2 % of the columns, up to 139: 30.6
+// against 23.5, 33.5 against 30.5.  2 % uniform, up to 55: 21.9 against 22.5, 26.9
+// against 30.4).
 // More than one round of workgroups has to be filled, in CUs and rows together, by
 // kRowsMinFill (4096 x 38400 at 64 rows, 300 workgroups, 0.59: 68.9 against 62.6 us;
 // 4096 x 28672 at 80 rows, 0.55: 67.6 against 67.7, at 128 rows, 0.88: 65.1 against
@@ -708,8 +713,9 @@ static bool rows_faster(const Plan& p, int rb, int blocks, int S, int64_t units,
 // every default launch fits the static scratch.
 void plan_rows(Plan* p, bool outliers) {
   p->rows_RB = 0;
-  if (p->M <= kRowsMinM || p->max_tile_groups > kRowsMaxGroups) return;
+  if (p->M <= kRowsMinM) return;
   const int rb = p->M <= 32 ? 1 : 2;
+  if (p->max_tile_groups > (rb == 1 ? kRowsMaxGroups32 : kRowsMaxGroups)) return;
   const int blocks = (p->M + 32 * rb - 1) / (32 * rb);
   const int n_cb = (p->N + fqk::kRowsCols - 1) / fqk::kRowsCols;
   const int64_t units = int64_t(n_cb) * blocks;
@@ -741,8 +747,7 @@ int launch_rows(const Plan& pl, const MatmulPtrs& p, bool sparse, bool two_group
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (pl.rows_RB == 1) {
     if (!sparse) return fqk::launch_rows_variant<1, false, 1>(pl, p, s);
-    return two_group_loads ? fqk::launch_rows_variant<1, true, 2>(pl, p, s)
-                           : fqk::launch_rows_variant<1, true, 1>(pl, p, s);
+    return fqk::launch_rows_variant<1, true, 1>(pl, p, s);   // tiles of one load, plan_rows sees to it
   }
   if (!sparse) return fqk::launch_rows_variant<2, false, 1>(pl, p, s);
   return two_group_loads ? fqk::launch_rows_variant<2, true, 2>(pl, p, s)

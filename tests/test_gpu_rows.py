@@ -27,7 +27,7 @@ CASES = [
     (96, 14336, 2048, 0.0004, None, 2, 8),      # two row blocks and a split, most tiles empty
     (128, 4096, 6144, 0.01, None, 2, 2),        # two full row blocks and a split
     (17, 1792, 16512, 0.02, None, 1, 1),        # one 32-row block
-    (32, 2048, 16448, 0.05, "column", 1, 1),    # one full 32-row block, more than 64 groups
+    (32, 2048, 16448, 0.012, "column", 1, 1),   # one full 32-row block, up to 62 groups a tile
     (40, 16256, 4096, 0.01, None, 1, 8),        # 127 tiles split 8 ways: 15 and 16
     (48, 1792, 16448, 0.0, None, 1, 1),         # no outliers: the dense-only form
     (80, 14336, 2048, 0.0, None, 2, 8),         # the same, two row blocks and a split
@@ -70,12 +70,15 @@ def test_rows_kernel_bit_exact(gpu_lib, M, K, N, frac, packing, row_blocks, spli
     assert np.array_equal(y.cpu().numpy()[:, cols], exact.astype(np.float32))
 
 
-@pytest.mark.parametrize("groups", [64, 65, 129, 160, 161])
-def test_rows_kernel_one_full_tile(gpu_lib, groups):
+@pytest.mark.parametrize("M,groups,kernel", [(50, 64, "rows"), (50, 65, "rows"), (50, 129, "rows"),
+                                             (50, 160, "rows"), (50, 161, "strip"),
+                                             (32, 64, "rows"), (32, 65, "strip")])
+def test_rows_kernel_one_full_tile(gpu_lib, M, groups, kernel):
     """Sparse tiles and one of `groups` groups: what one group load leaves is
-    loaded inside the tile, and past 160 groups the strip kernel runs."""
+    loaded inside the tile; past 160 groups, past 64 with 32-row blocks, the
+    strip kernel runs."""
     fq = gpu_lib
-    M, K, N = 50, 1792, 16448
+    K, N = 1792, 16448
     p = make_exact_problem(M, K, N, frac=0.0, seed=groups)
     rng = np.random.Generator(np.random.PCG64(groups))
     pos = rng.choice(128 * 64, size=4 * groups - 1, replace=False)
@@ -85,7 +88,7 @@ def test_rows_kernel_one_full_tile(gpu_lib, groups):
     p = dataclasses.replace(p, k=k, n=n, v=bf16_bits_from_f32(v.astype(np.float32)))
     host = fq.fq_pack_tile_coo(K, N, p.k, p.n, p.v)
     assert host.sizes.max_tile_groups == groups
-    assert fq.fq_launch_kernel(M, K, N, host)["kernel"] == ("rows" if groups <= 160 else "strip")
+    assert fq.fq_launch_kernel(M, K, N, host)["kernel"] == kernel
     X, Wq, s, z = fq.to_device(p)
     print(f"rows kernel, one tile of {groups} groups", flush=True)
     y = fq.fq_w4a16_outlier_matmul(X, Wq, s, z, fq.TileCOODevice(host), y_dtype="f32")

@@ -656,6 +656,11 @@ def test_launch_kernel_names_what_runs(lib):
     # the fullest tile's limit
     assert fq.fq_launch_kernel(128, K, N, _uniform(K, N, 60, 160))["kernel"] == "rows"
     assert fq.fq_launch_kernel(128, K, N, _uniform(K, N, 60, 161))["kernel"] == "strip"
+    for M in (17, 32):
+        assert fq.fq_launch_kernel(M, K, N, _uniform(K, N, 41, 64))["kernel"] == "rows"
+        assert fq.fq_launch_kernel(M, K, N, _uniform(K, N, 21, 65))["kernel"] == "strip"
+        assert fq.fq_launch_kernel(M, K, N, _uniform(K, N, 103, 124))["kernel"] == "strip"
+    assert fq.fq_launch_kernel(33, K, N, _uniform(K, N, 21, 65))["kernel"] == "rows"
     # a workspace for the strip kernel's partial sums only gets that kernel
     K, N, tc = 7296, 8192, _uniform(7296, 8192, 21)
     need = fq.fq_workspace_bytes(64, K, N)
